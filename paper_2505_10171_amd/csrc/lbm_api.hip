@@ -33,7 +33,8 @@ hipError_t launch_moments(const Batch& b, int storage, unsigned nblk, unsigned m
                           hipStream_t st);
 hipError_t launch_init_mask(const SimDev& s, hipStream_t st);
 hipError_t launch_init_pops(const SimDev& s, void* pops, hipStream_t st);
-hipError_t launch_mass(const SimDev& s, const float* rp, double* acc, hipStream_t st);
+hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, double* acc,
+                       hipStream_t st);
 hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
 hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
                               hipStream_t st);
@@ -86,7 +87,7 @@ struct SimLayout {
   long long N;
   int np, Bmask, Bcap, hist_cap;
   size_t pop_bytes, fresh_cap;
-  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_mask, off_claim, off_fresh, off_fresh_own,
+  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_claim, off_fresh, off_fresh_own,
       off_counters, off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_caporg, off_mass,
       off_step;
   size_t total;
@@ -160,6 +161,12 @@ bool valid_particle(const lbm_config& c, const lbm_particle& p, char* msg, size_
   return true;
 }
 
+}  // namespace
+
+static void set_mom_tiling(SimDev& d, int planes = 0);
+
+namespace {
+
 SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
   SimLayout L{};
   L.N = (long long)c.nx * c.ny * c.nz;
@@ -184,6 +191,14 @@ SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
   L.off_rp1 = take(8 * L.N);
   L.off_nrm = take(16 * L.N);
   L.off_cur = take(8 * L.N);
+  {
+    SimDev t{};
+    t.nx = c.nx;
+    t.ny = c.ny;
+    t.nz = c.nz;
+    set_mom_tiling(t);
+    L.off_kind = take((size_t)t.mtiles_x * t.mtiles_y * t.nz);
+  }
   L.off_mask = take(2 * L.N);
   L.off_claim = take(4 * L.N);
   L.off_fresh = take(4 * L.fresh_cap);
@@ -346,7 +361,7 @@ static void set_tile(SimDev& d, int tx) {
 // partial round of long blocks leaves most CUs idle (the 400 x 181 x 71 run:
 // interface + moments 268 us at 12 planes, 245 us at 6; the 512 x 256 x 192
 // slab and boxes of under one round are within 1 % either way).
-static void set_mom_tiling(SimDev& d, int planes = 0) {
+static void set_mom_tiling(SimDev& d, int planes) {
   d.mtile_x = 16;
   for (int w : {64, 32}) {
     if (100LL * ((d.nx + w - 1) / w) * w <= 120LL * d.nx) {
@@ -601,6 +616,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     d.rp[1] = (float*)(b + sh.L.off_rp1);
     d.nrm = (float*)(b + sh.L.off_nrm);
     d.curv = (float2*)(b + sh.L.off_cur);
+    d.kind = (uint8_t*)(b + sh.L.off_kind);
     d.mask = (uint16_t*)(b + sh.L.off_mask);
     d.claim = (uint32_t*)(b + sh.L.off_claim);
     d.fresh = (uint32_t*)(b + sh.L.off_fresh);
@@ -1185,7 +1201,7 @@ int lbm_mass(lbm_ctx* ctx, int32_t sim, double out[2]) {
   if (!sh) return set_err(ctx, LBM_ERANGE, "simulation index out of range");
   SimDev& d = sh->d;
   HIPCHK(ctx, launch_zero_f64(d.mass_acc, 2, ctx->stream));
-  HIPCHK(ctx, launch_mass(d, d.rp[ctx->rd ^ 1], d.mass_acc, ctx->stream));
+  HIPCHK(ctx, launch_mass(d, d.rp[ctx->rd ^ 1], d.pops[ctx->cur], d.mass_acc, ctx->stream));
   HIPCHK(ctx, hipMemcpyAsync(out, d.mass_acc, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
   return lbm_sync(ctx);
 }
@@ -1207,7 +1223,7 @@ int lbm_mass_all_noalloc(lbm_ctx* ctx, double* out, int32_t dst_is_device) {
   HIPCHK(ctx, launch_zero_f64(acc, 2 * n, st));
   for (int si = 0; si < n; ++si) {
     const SimDev& d = ctx->sims[si].d;
-    HIPCHK(ctx, launch_mass(d, d.rp[ctx->rd ^ 1], acc + 2 * si, st));
+    HIPCHK(ctx, launch_mass(d, d.rp[ctx->rd ^ 1], d.pops[ctx->cur], acc + 2 * si, st));
   }
   HIPCHK(ctx, hipMemcpyAsync(out, acc, 2 * sizeof(double) * (size_t)n,
                              dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));

@@ -48,6 +48,11 @@ constexpr uint16_t FRESH_BIT = 0x8000;
 // stands for the nodes beyond an open end
 constexpr float PHI_SOLID = 4.0f;
 constexpr float PHI_SOLID_TEST = 2.0f;  // phi above this marks a solid node
+// a fluid node's phi other than exactly +-1
+__host__ __device__ inline bool phi_pure(float phi) { return fabsf(phi) == 1.0f; }
+__host__ __device__ inline bool phi_mixed(float phi) {
+  return !phi_pure(phi) && !(phi > PHI_SOLID_TEST);
+}
 __host__ __device__ inline float solid_phi(uint32_t mask_code) { return PHI_SOLID + (float)mask_code; }
 
 // -------------------------------------------------------------- particles
@@ -173,12 +178,17 @@ struct SimDev {
   // fields
   void* pops[2];       // ping-pong population buffers: 19 planes of N (f only)
   // per-node moments of a state, 2 planes of N: rho, then phi (rho0 and
-  // PHI_SOLID at solids); rp[rd ^ 1] belongs to the state in pops[cur], rp[rd]
-  // to the state before it (the FP16 reference of pops[cur])
+  // solid_phi at solids); rp[rd ^ 1] belongs to the state in pops[cur], rp[rd]
+  // to the state before it (the FP16 reference of pops[cur]).  FP32 storage
+  // keeps rho only where phi is not exactly +-1 and at the nodes next to solids
+  // once the state has collided: in a pure fluid it is the sum of the
+  // populations, which whoever needs it forms (node_density)
   float* rp[2];
   float* nrm;          // 4 planes of N: n_x, n_y, n_z (NaN at solids), |G| (-1 at solids)
-
   float2* curv;        // per node (CSF coefficient, solid-neighbour bits as float)
+  // per plane z of each x-y tile of the moments tiling (index
+  // (z mtiles_y + tile y) mtiles_x + tile x), a TileKind of the colliding state
+  uint8_t* kind;
   uint16_t* mask;      // 0 fluid, 1 wall, 2+p particle p; FRESH_BIT while refilling
   uint32_t* claim;     // per node: lowest particle claiming it in the new mask, ~0u none
   uint32_t* fresh;     // fresh-node list: node index
@@ -238,6 +248,34 @@ __device__ __forceinline__ bool tile_node(const SimDev& s, int lb, int& n, int& 
   n = gx + nx * (gy + ny * gz);
   return true;
 }
+
+// What the interface pass found around one plane of an x-y tile, over the
+// tile grown by two nodes and the two planes below and above: nodes of both
+// fluids or of phi other than +-1 (KIND_MIXED), or one pure fluid (phi exactly
+// +1 or -1 at every fluid node), without or with solid nodes or an open end.
+// On a pure tile plane the normal, the CSF coefficient and |G| are exactly zero
+// and phi stays what it is.  With FP32 storage the interface pass then writes
+// none of them (nor, with no solid near, the curvature word), and nothing
+// reads them there.  With FP16 storage it writes the zeros: the fused kernel,
+// bound by its arithmetic there, took 576 us with the tests and 556 without
+// them where no tile plane is pure (512 x 256 x 192).
+// What it is worth depends on how much of the box is exactly pure: one fluid in
+// a tube (320 x 83 x 83) 201 -> 145 us per step; the 512 x 256 x 192 slab over
+// its first 300 steps (7 of 10 tile planes pure after 100, 3 in 100 after 500,
+// as the rounding of the colour sums spreads) 2.25 -> 2.01 ms; where no plane is
+// pure the tests cost 0.9 to 1.5 % of the fused kernel (256 x 128 x 96:
+// 91.3 -> 92.7 us) and 1 % of the moments pass.
+enum TileKind : uint8_t {
+  KIND_MIXED = 0,
+  KIND_PURE_A = 1,  // phi = +1
+  KIND_PURE_B = 2,  // phi = -1
+  KIND_PURE_A_SOLID = 3,
+  KIND_PURE_B_SOLID = 4
+};
+__device__ __forceinline__ unsigned kind_index(const SimDev& s, int x, int y, int z) {
+  return (unsigned)((z * s.mtiles_y + (y >> (8 - s.mtile_lx))) * s.mtiles_x + (x >> s.mtile_lx));
+}
+__device__ __forceinline__ float pure_sign(int kind) { return (kind & 1) ? 1.0f : -1.0f; }
 
 enum StatusBits : uint32_t {
   ST_UNSTABLE = 1u,
@@ -440,16 +478,35 @@ __device__ __forceinline__ void colour_sums(const float* d, CSRC cs_src, const v
 
 // Colour source (phi, r n_x, r n_y, r n_z) of node m of the state that
 // collided, r = beta rho (1 - phi^2) / 2, from its moments RO (rho plane, phi
-// plane) and normal planes NX; NaN in r n at a solid node (its normal is NaN).
+// plane) and normal planes NX; NaN in r n at a solid node.  At phi = +-1 r is
+// zero and the normal is not looked at (a pure tile plane holds none).  The
+// selects are on the normal, not on the products: the compiler contracts r n
+// into the sums where a record stays in registers, and still does.
 __device__ __forceinline__ v4f colour_record(float rho, float phi, float nx, float ny, float nz,
                                              float hb) {
   const float r = hb * rho * (1.0f - phi) * (1.0f + phi);
+  const float none = phi > PHI_SOLID_TEST ? __int_as_float(0x7fc00000) : 0.0f;
+  const bool mixed = phi_mixed(phi);
+  nx = mixed ? nx : none;
+  ny = mixed ? ny : none;
+  nz = mixed ? nz : none;
   return v4f{phi, r * nx, r * ny, r * nz};
 }
 __device__ __forceinline__ v4f colour_source(const GLB float* RO, const GLB float* NX, int N,
                                              int m, float hb) {
   const unsigned u = (unsigned)m;
   return colour_record(at(RO, u), at(RO + N, u), at(NX, u), at(NX + N, u), at(NX + 2 * N, u), hb);
+}
+
+// rho = sum f_i of a node as the moments pass sums it, from its populations
+template <int STORE, class PT>
+__device__ __forceinline__ float node_density(PT pops, int N, int n, float rho0, float Rd) {
+  float d[Q];
+  load_pops<STORE>(pops, N, n, rho0, Rd, d);
+  float r = __fmaf_rn(wq(0), rho0, d[0]);
+#pragma unroll
+  for (int i = 1; i < Q; ++i) r += __fmaf_rn(wq(i), rho0, d[i]);
+  return r;
 }
 
 // both, for one node, with the colour sources read from the global planes

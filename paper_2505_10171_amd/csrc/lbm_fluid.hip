@@ -161,6 +161,8 @@ __device__ __forceinline__ int xcd_tile(int lin, int nblk) {
 // A block takes an x-y tile of the simulation's moments tiling and marches up
 // s.mkz planes.  The colour sources of three planes of the tile grown by one
 // node sit in an LDS ring; each plane adds the sources of the plane above.
+// A pure tile plane (TileKind) takes no sources and, in FP32, no populations:
+// its phi stays, and its density is not kept.
 constexpr int MOM_HALO = 66 * 6;  // largest tile plane grown by one: (64 + 2)(4 + 2)
 // LX: log2 of the tiles' x width when the launch fixes it (the tile's LDS
 // offsets are then immediates), 0 to read it from the simulation
@@ -209,9 +211,21 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
   const float qnan = __int_as_float(0x7fc00000);
   const v4f open_rec = v4f{qnan, qnan, qnan, qnan};
   auto zwrap = [&](int z) { return z < 0 ? z + nz : (z >= nz ? z - nz : z); };
-  // planes z0 - 1 and z0 into the ring
+  // the kinds of the block's tile planes (entry zz + 1; mixed ones bound by
+  // pure ones below and above)
+  __shared__ uint8_t kinds[258];
+  {
+    const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
+    if (t < 2) kinds[t * (kz + 1)] = KIND_PURE_A;
+    if (t < kz) kinds[t + 1] = KIND[((z0 + t) * s.mtiles_y + by) * s.mtiles_x + bx];
+  }
+  __syncthreads();
+  auto kind_of = [&](int zz) { return __builtin_amdgcn_readfirstlane((int)kinds[zz + 1]); };
+  int k0 = kind_of(0), k1 = kz > 1 ? kind_of(1) : KIND_PURE_A;
+  // planes z0 - 1 and z0 into the ring, if a mixed plane reads them
 #pragma unroll
   for (int dz = 0; dz < 2; ++dz) {
+    if (k0 != KIND_MIXED && (dz == 0 || k1 != KIND_MIXED)) continue;
     const int zp = zwrap(z0 - 1 + dz);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -238,6 +252,26 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
   };
   const int gxc = min(gx, nx - 1), gyc = min(gy, ny - 1);
   const float rho0 = s.rho0;  // kept in a register: the stores below may alias s
+  // a pure tile plane: phi of its fluid nodes stays what it is (every source
+  // of the colour is the same pure fluid).  FP16 needs the density as the
+  // next state's reference; FP32 keeps none there, so that the populations of
+  // the pure fluids are not read at all
+  auto pure_plane = [&](int z, float phi) {
+    if (!in) return;
+    const int n = gx + nx * (gy + ny * z);
+    const uint16_t m = MASK[n];
+    if (m & FRESH_BIT) {
+      MASK[n] = (uint16_t)(m & ~FRESH_BIT);
+      return;
+    }
+    if (m != 0) {
+      RN[n] = rho0;
+      RN[N + n] = solid_phi(m);
+      return;
+    }
+    if (STORE) RN[n] = node_density<STORE>(pops, N, n, rho0, RO[n]);
+    RN[N + n] = phi;
+  };
   // a plane's results are stored once the next plane's loads are in, so that
   // they are in flight during the sums instead of ahead of the next loads
   int pn = -1;
@@ -257,6 +291,23 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
   };
   for (int zz = 0; zz < kz; ++zz) {
     const int z = z0 + zz;
+    const int kind = k0, above = k1;
+    k0 = k1;
+    k1 = zz + 2 < kz ? kind_of(zz + 2) : KIND_PURE_A;
+    if (kind != KIND_MIXED) {
+      // its plane above is read by the mixed planes z + 1 and z + 2
+      if (above == KIND_MIXED || k1 == KIND_MIXED) {
+        fetch_raw(z);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (hon[j])
+            ring[(z + 1) % 3][k_of(t, j)] =
+                hoff[j] < 0 ? open_rec
+                            : colour_record(sr[j][0], sr[j][1], sr[j][2], sr[j][3], sr[j][4], hb);
+      }
+      pure_plane(z, pure_sign(kind));
+      continue;
+    }
     const int n = gxc + nx * (gyc + ny * z);
     float d[Q];
     const uint16_t m = MASK[n];
@@ -337,15 +388,24 @@ __global__ void k_init_pops(SimDev s, void* pops) {
 // --------------------------------------------------------- global mass (FP64)
 // masses of fluids a and b, sum of rho (1 +- phi) / 2 over fluid nodes, from
 // the moments rp (rho plane, phi plane) of the current state, added into
-// acc[0], acc[1] (cleared by the caller)
+// acc[0], acc[1] (cleared by the caller).  FP32 keeps no density where phi is
+// +-1: it is summed from the populations there
+template <int STORE>
 __global__ __launch_bounds__(256) void k_mass(SimDev s, const float* __restrict__ rp,
+                                              const void* __restrict__ pops,
                                               double* __restrict__ acc) {
+  using T = typename Codec<STORE>::T;
   __shared__ double sh[2][256];
   double a = 0.0, b = 0.0;
   for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < s.N;
        n += (long long)gridDim.x * blockDim.x) {
     if (s.mask[n] != 0) continue;
-    const double rho = (double)rp[n], sg = rho * (double)rp[s.N + n];
+    const float phi = rp[s.N + n];
+    const double rho = STORE == 0 && phi_pure(phi)
+                           ? (double)node_density<STORE>(gp((const T*)pops), (int)s.N, (int)n,
+                                                         s.rho0, 0.f)
+                           : (double)rp[n];
+    const double sg = rho * (double)phi;
     a += 0.5 * (rho + sg);
     b += 0.5 * (rho - sg);
   }
@@ -551,51 +611,155 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   };
   const std::integral_constant<bool, true> with_solids;
   const std::integral_constant<bool, false> no_solids;
-  auto has_solid = [&](const float* v) {
-    bool r = false;
+  // the normals of a plane whose phi planes hold one pure fluid: zero (NaN
+  // at its solid nodes, if it may have any)
+  auto zero_normals = [&](int z, bool solids) {
+    const int sl = nslot(z);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) r |= fon[j] && v[j] > PHI_SOLID_TEST;
-    return (int)r;
+    for (int j = 0; j < 2; ++j)
+      if (hon[j]) {
+        const bool sd =
+            solids && fring[fslot(z)][(hx_[j] + 1) + FX * (hy_[j] + 1)] > PHI_SOLID_TEST;
+        const float v = sd ? qnan : 0.f;
+        const int k = hx_[j] + HX * hy_[j];
+        nrx[sl][k] = v;
+        nry[sl][k] = v;
+        nrz[sl][k] = v;
+        const int tlx = hx_[j] - 1, tly = hy_[j] - 1;
+        if (tlx >= 0 && tlx < tx && tly >= 0 && tly < ty) nrg[sl][tlx + tx * tly] = sd ? -1.f : 0.f;
+      }
   };
+  // what a phi plane of the grown tile holds: 1 phi = +1, 2 phi = -1, 4 a fluid
+  // node of any other phi, 8 a solid (or open-end) node; each wave's word into
+  // wcls, to be combined behind a barrier (two buffers in turn: a pure plane
+  // passes one barrier only)
+  __shared__ uint32_t wcls[2][4];
+  auto classify = [&](const float* v, int shift) -> uint32_t {
+    bool sd = false;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) sd |= fon[j] && v[j] > PHI_SOLID_TEST;
+    uint32_t c = __ballot(sd) ? 8u : 0u;
+    // in the interface one value per lane tells (entry 0 always holds a node)
+    if (__ballot(phi_mixed(v[0]))) {
+      c |= 4u;
+    } else {
+      bool a = false, b = false, o = false;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        a |= fon[j] && v[j] == 1.0f;
+        b |= fon[j] && v[j] == -1.0f;
+        o |= fon[j] && phi_mixed(v[j]);
+      }
+      c |= (__ballot(a) ? 1u : 0u) | (__ballot(b) ? 2u : 0u) | (__ballot(o) ? 4u : 0u);
+    }
+    return c << shift;
+  };
+  auto block_class = [&](int b) -> uint32_t {
+    return __builtin_amdgcn_readfirstlane(wcls[b][0] | wcls[b][1] | wcls[b][2] | wcls[b][3]);
+  };
+  // one pure fluid (or only solids) in planes of the given classes
+  auto pure_class = [](uint32_t c) { return (c & 4u) == 0u && (c & 3u) != 3u; };
   // prologue: phi of planes z0 - 2 .. z0 + 1, normals of planes z0 - 1, z0
-  int psol = 0;
+  uint32_t pcls = 0;
   {
     float v[3];
     for (int dz = -2; dz <= 1; ++dz) {
       load_phi(z0 + dz, v);
       store_phi(z0 + dz, v);
-      psol |= has_solid(v);
+      pcls |= classify(v, 4 * (1 - dz));
     }
   }
   float nxt[3];
   load_phi(z0 + 2, nxt);
-  // bit k: a solid in phi plane (z + 2 - k) of the current plane z, once the
-  // loop has shifted in plane z + 2 (the prologue's planes all take the
-  // block's flag over the four)
-  uint32_t hist = __syncthreads_or(psol) ? 0xFu : 0u;
-  if (hist) {
-    normals(z0 - 1, with_solids);
-    normals(z0, with_solids);
-  } else {
-    normals(z0 - 1, no_solids);
-    normals(z0, no_solids);
+  if ((t & 63) == 0) wcls[1][t >> 6] = pcls;
+  __syncthreads();
+  // four bits for each of the phi planes z + 2 - k (k = 0 .. 4) of the current
+  // plane z, once the loop has shifted in plane z + 2
+  uint32_t hist = block_class(1);
+  {
+    // planes z0 - 2 .. z0 and z0 - 1 .. z0 + 1
+    const uint32_t lo = (hist >> 4) | (hist >> 8) | (hist >> 12), hi = hist | (hist >> 4) | (hist >> 8);
+    if (pure_class(lo & 15u))
+      zero_normals(z0 - 1, (lo & 8u) != 0u);
+    else if (lo & 8u)
+      normals(z0 - 1, with_solids);
+    else
+      normals(z0 - 1, no_solids);
+    if (pure_class(hi & 15u))
+      zero_normals(z0, (hi & 8u) != 0u);
+    else if (hi & 8u)
+      normals(z0, with_solids);
+    else
+      normals(z0, no_solids);
   }
   __syncthreads();  // the loop's first phi store reuses the slot of plane z0 - 2
   // kept in a register: read from s after the stores below, it would be a
   // load behind them (they may alias s) and its wait would wait for them too
   const float csf = -0.5f * s.sigma;
+  const int s_mtx = s.mtiles_x, s_mty = s.mtiles_y;
+  const bool fp16 = s.storage != 0;
+  GLB uint8_t* __restrict__ KIND = gp(s.kind);
   for (int zz = 0; zz < kz; ++zz) {
     const int z = z0 + zz;
     store_phi(z + 2, nxt);
-    hist = (hist << 1) | (__syncthreads_or(has_solid(nxt)) ? 1u : 0u);
+    {
+      const uint32_t c = classify(nxt, 0);
+      if ((t & 63) == 0) wcls[zz & 1][t >> 6] = c;
+    }
+    __syncthreads();
+    hist = (hist << 4) | block_class(zz & 1);
     if (zz + 1 < kz) load_phi(z + 3, nxt);
-    if (hist & 7u)  // planes z .. z + 2
+    const uint32_t near = hist | (hist >> 4) | (hist >> 8);  // planes z .. z + 2
+    const uint32_t all = near | (hist >> 12) | (hist >> 16);  // planes z - 2 .. z + 2
+    const bool pure = pure_class(all & 15u);
+    if (t == 0)
+      KIND[(z * s_mty + by) * s_mtx + bx] =
+          !pure ? KIND_MIXED
+                : (uint8_t)(((all & 2u) ? KIND_PURE_B : KIND_PURE_A) + ((all & 8u) ? 2 : 0));
+    if (pure_class(near & 15u))
+      zero_normals(z + 1, (near & 8u) != 0u);
+    else if (near & 8u)
       normals(z + 1, with_solids);
     else
       normals(z + 1, no_solids);
+    if (pure) {
+      // no normal, curvature or |G|; the solid-neighbour bits where there are
+      // solids, from phi.  Without solids nothing of the rings is read here, and the
+      // next plane's barrier orders the zeros just written
+      uint32_t bits = 0u;
+      if (all & 8u) {
+        if (in) {
+          const int n = gx + nx * (gy + ny * z);
+          const int c = (lx + 2) + FX * (ly + 2);
+          bits = 0x80000000u;
+          if (!(fring[fslot(z)][c] > PHI_SOLID_TEST)) {
+            bits = 0u;
+// (not unrolled: its eighteen addresses, hoisted, would spill the
+            // registers of the curvature)
+#pragma unroll 1
+            for (int i = 1; i < Q; ++i)
+              bits |= fring[fslot(z + cz(i))][c + cx(i) + FX * cy(i)] > PHI_SOLID_TEST ? (1u << i) : 0u;
+          }
+          if (!fp16) CUR[2 * n + 1] = __uint_as_float(bits);
+        }
+        __syncthreads();
+      }
+      if (fp16 && in) {
+        const int n = gx + nx * (gy + ny * z);
+        const bool sd = bits >> 31;
+        const float v = sd ? qnan : 0.f;
+        NX[n] = v;
+        NX[N + n] = v;
+        NX[2 * N + n] = v;
+        NX[3 * N + n] = sd ? -1.f : 0.f;
+        CUR[2 * n] = 0.f;
+        CUR[2 * n + 1] = __uint_as_float(bits);
+      }
+      continue;
+    }
     __syncthreads();
     // the curvature reads the normals of planes z - 1 .. z + 1
-    const bool csol = (hist & 0xEu) != 0u;
+    const bool csol = (hist & 0x8880u) != 0u;
     if (in && !csol) {
       const int c0 = (lx + 1) + HX * (ly + 1);
       const int n = gx + nx * (gy + ny * z);
@@ -696,7 +860,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   const GLB T* __restrict__ sp_ = gp((const T*)s.pops[bt.cur]);
   GLB T* __restrict__ dp_ = gp((T*)s.pops[bt.cur ^ 1]);
   const GLB float* __restrict__ NX = gp((const float*)s.nrm);
-  const GLB float* __restrict__ cur = gp((const float*)s.curv);
   // moments of this state (rho, phi planes) and of the one before it; FP16
   // decodes with the latter's density and encodes with the former's
   const GLB float* __restrict__ RM = gp((const float*)s.rp[bt.rd ^ 1]);
@@ -707,10 +870,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   if (!tile_node(s, sb.y, n, gx, gy, gz)) return;
   const float rho0 = s.rho0;
   const float inv_rho0 = 1.0f / rho0;
-  const float2 cb = make_float2(at(cur, 2u * (unsigned)n), at(cur, 2u * (unsigned)n + 1u));
-  const uint32_t bits = __float_as_uint(cb.y);
-
-  if (bits & 0x80000000u) {
+  // on a pure tile plane the normal and the CSF coefficient are zero, phi is
+  // known, and without solids near so are the neighbour bits: none is loaded
+  const GLB float* __restrict__ cur = gp((const float*)s.curv);
+  const int kind =
+      STORE ? KIND_MIXED : gp((const uint8_t*)s.kind)[kind_index(s, gx, gy, gz)];
+  uint32_t bits = 0u;
+  if (kind >= KIND_PURE_A_SOLID) bits = __float_as_uint(at(cur, 2u * (unsigned)n + 1u));
+  auto solid_node = [&]() {
     if (MODE == MODE_FIELDS) {
       const uint16_t m0 = s.mask[n];
       float ux = 0.f, uy = 0.f, uz = 0.f;
@@ -732,6 +899,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
       out_F[N + n] = 0.f;
       out_F[2 * N + n] = 0.f;
     }
+  };
+  if (bits & 0x80000000u) {
+    solid_node();
     return;
   }
   const Nbr nb(gx, gy, gz, nx, ny, nz);
@@ -747,9 +917,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   float Rd[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) Rd[i] = STORE ? at(RM, (unsigned)(i == 0 ? n : nb(i))) : 0.f;
-  const float3 nc =
-      make_float3(at(NX, (unsigned)n), at(NX + N, (unsigned)n), at(NX + 2 * N, (unsigned)n));
-  const float phi = at(RM + N, (unsigned)n);
+  float3 nc = make_float3(0.f, 0.f, 0.f);
+  float phi = pure_sign(kind), cb = 0.f;
+  if (kind == KIND_MIXED) {
+    nc = make_float3(at(NX, (unsigned)n), at(NX + N, (unsigned)n), at(NX + 2 * N, (unsigned)n));
+    phi = at(RM + N, (unsigned)n);
+    cb = at(cur, 2u * (unsigned)n);
+    // here with the populations, not before them: few nodes of a mixed tile
+    // plane are solid, and the wait would come before every load
+    bits = __float_as_uint(at(cur, 2u * (unsigned)n + 1u));
+    if (bits & 0x80000000u) {
+      solid_node();
+      return;
+    }
+  }
   float drho = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -761,9 +942,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   const float rho = rho0 + drho;
   // force: CSF surface tension c n + body force on fluid a (weight (1+phi)/2)
   const float fa = 0.5f * (1.0f + phi);
-  const float Fx = cb.x * nc.x + s.body[0] * fa;
-  const float Fy = cb.x * nc.y + s.body[1] * fa;
-  const float Fz = cb.x * nc.z + s.body[2] * fa;
+  const float Fx = cb * nc.x + s.body[0] * fa;
+  const float Fy = cb * nc.y + s.body[1] * fa;
+  const float Fz = cb * nc.z + s.body[2] * fa;
   const float irho = 1.0f / rho;
   const float ux = (jx + 0.5f * Fx) * irho;
   const float uy = (jy + 0.5f * Fy) * irho;
@@ -782,6 +963,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     return;
   }
   if (!(rho > 0.f) || !(uu <= 0.09f)) atomicOr(&s.counters[1], (uint32_t)ST_UNSTABLE);
+  // next to a solid FP32 keeps the density of the colliding state for the link
+  // kernel
+  if (STORE == 0 && bits != 0u) gp(s.rp[bt.rd ^ 1])[n] = rho;
   // local relaxation: harmonic mean of the kinematic viscosities
   const float inv_nu = (1.0f + phi) * s.inv2nua + (1.0f - phi) * s.inv2nub;
   const float om = 1.0f / (0.5f + 3.0f / inv_nu);
@@ -1063,12 +1247,16 @@ hipError_t launch_init_pops(const SimDev& s, void* pops, hipStream_t st) {
   return hipGetLastError();
 }
 
-// rp: moments (rho plane, phi plane) of the current state; acc: 2 doubles,
-// cleared before
-hipError_t launch_mass(const SimDev& s, const float* rp, double* acc, hipStream_t st) {
+// rp: moments (rho plane, phi plane) of the current state, pops its
+// populations; acc: 2 doubles, cleared before
+hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, double* acc,
+                       hipStream_t st) {
   unsigned nb = nblocks(s.N, 256);
   if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_mass, dim3(nb), dim3(256), 0, st, s, rp, acc);
+  if (s.storage == 0)
+    hipLaunchKernelGGL(k_mass<0>, dim3(nb), dim3(256), 0, st, s, rp, pops, acc);
+  else
+    hipLaunchKernelGGL(k_mass<1>, dim3(nb), dim3(256), 0, st, s, rp, pops, acc);
   return hipGetLastError();
 }
 

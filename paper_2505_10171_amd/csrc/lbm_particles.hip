@@ -175,8 +175,12 @@ __global__ __launch_bounds__(256) void k_refill(Batch bt) {
             rebuild_moments<STORE>(gp((const T*)b), RO, gp((const float*)s.nrm), N, m, nbm,
                                    s.rho0, 0.5f * s.beta, STORE ? RO[m] : 0.f, rho, sg);
           } else {
-            rho = RN[m];
-            sg = rho * RN[N + m];
+            // FP32 keeps no density where phi is +-1
+            const float ph = RN[N + m];
+            rho = STORE == 0 && phi_pure(ph)
+                      ? node_density<STORE>(gp((const T*)b), N, m, s.rho0, 0.f)
+                      : RN[m];
+            sg = rho * ph;
           }
           ra = 0.5f * (rho + sg);
           rb = 0.5f * (rho - sg);
@@ -247,6 +251,7 @@ __global__ void k_capbox(Batch bt) {
   const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
   const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd]) + N;
   const GLB float* __restrict__ NRM = gp((const float*)s.nrm);
+  const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
   // a particle whose box holds no fluid node with |G| near EPS_G or above gets
   // no force: every point's G is a convex combination of corner values, so it
   // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
@@ -260,12 +265,14 @@ __global__ void k_capbox(Batch bt) {
     // used only inside a branch is made there, a second round trip)
     const float gw = at(NRM + 3 * N, n), ph = at(PHI, n);
     const float n0 = at(NRM, n), n1 = at(NRM + N, n), n2 = at(NRM + 2 * N, n);
+    const uint8_t kind = KIND[kind_index(s, x, y, z)];
     // G = n max(|G|, EPS_G): the colour gradient after the wetting rotation;
-    // phi = 2 marks a solid node
-    const bool fl = gw >= 0.f;
+    // phi = 2 marks a solid node; on a pure tile plane G is zero and its
+    // normal planes are not looked at
+    const bool fl = !(ph > PHI_SOLID_TEST), mixed = fl && kind == KIND_MIXED;
     const float gm = fmaxf(gw, EPS_G);
-    const float4 v = make_float4(fl ? ph : 2.f, fl ? n0 * gm : 0.f, fl ? n1 * gm : 0.f,
-                                 fl ? n2 * gm : 0.f);
+    const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
+                                 mixed ? n2 * gm : 0.f);
     box[k] = v;
     iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
   }
