@@ -276,11 +276,12 @@ int lbm_set_tile(lbm_ctx* ctx, int32_t sim, int32_t tile_x);
  * whose whole tiles cover the box's width with at most 20 % to spare, else
  * 16 x 16) and marches up `planes` planes (1..256; 0 restores the default: 12 on planes
  * of at least 65,536 nodes unless that gives between 1,536 and 6,144 blocks,
- * else 6, or 8 where 6 gives more than 1,536 blocks and 8 at most 1,536; a
- * context of several simulations whose blocks at depth 24 number at least
- * 6,144 starts every simulation at 24).  Results are identical with any depth;
- * deeper blocks re-read fewer halo planes, shallower ones give more blocks
- * to fill the GPU. */
+ * else 6, or 8 where 6 gives more than 1,536 blocks and 8 at most 1,536; fewer
+ * where the context's blocks would number less than 512: the largest depth
+ * that gives 512, or single planes; a context of several simulations whose
+ * blocks at depth 24 number at least 6,144 marches 24 in every simulation).
+ * Results are identical with any depth; deeper blocks re-read fewer halo
+ * planes, shallower ones give more blocks to fill the GPU. */
 int lbm_set_march(lbm_ctx* ctx, int32_t sim, int32_t planes);
 
 /* Graph replay of steps.  With enable = 1, lbm_step captures two consecutive

@@ -25,7 +25,7 @@
 #include "lbm_device.h"
 
 namespace lbm {
-hipError_t launch_interface(const Batch& b, unsigned nblk, unsigned mnblk, hipStream_t st);
+hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st);
 hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int mode, float* orho,
                         float* ou, float* ophi, float* oF, hipStream_t st);
 hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, hipStream_t st);
@@ -276,6 +276,8 @@ struct SimHost {
   SimLayout L;
   SimDev d;
   double Rmax;
+  int march = 0;  // marching depth set by hand, 0: the default
+  int solo = 0;   // marching depth of launches over this simulation alone
 };
 
 // Per-phase timing with HIP events on the context's stream: per step six
@@ -387,8 +389,52 @@ static void set_mom_tiling(SimDev& d, int planes) {
   d.mtiles_y = (d.ny + ty - 1) / ty;
   d.mtiles_z = (d.nz + d.mkz - 1) / d.mkz;
 }
-static unsigned mom_blocks(const SimDev& d) {
-  return (unsigned)((long long)d.mtiles_x * d.mtiles_y * d.mtiles_z);
+// blocks of the moments tiling (mkz: the launch's depth, 0: the simulation's own)
+static unsigned mom_blocks(const SimDev& d, int mkz = 0) {
+  const int mz = mkz > 0 ? (d.nz + mkz - 1) / mkz : d.mtiles_z;
+  return (unsigned)((long long)d.mtiles_x * d.mtiles_y * mz);
+}
+
+// The default marching depths of the simulations of a context (those set by
+// hand are kept).  Each box starts from set_mom_tiling's.  A batch whose blocks
+// fill the GPU several times over even at a depth of 24 planes marches 24 (each
+// block re-reads its two halo planes once per 24 planes, not per 6 or 12;
+// measured on the ensemble of 256 boxes 48 to 96 wide: 8.75 ms per step at the
+// single-box depths, 8.54 at 12, 8.36 at 24).  A batch of fewer than 512 blocks
+// (two per CU) takes the largest depth that gives 512, or single planes: a block's
+// planes are a serial chain (interface + moments of a 32^3 box 38 us at 6
+// planes, 24 at 2, 20 at 1; 48^3 40, 25, 23; 64^3 37, 26, 26; 96^3, with 576
+// blocks at 6 planes, 55, 61, 70).
+constexpr long long MARCH_MIN_BLOCKS = 512;
+static void default_march(std::vector<SimHost>& sims, bool alone) {
+  long long deep = 0;
+  for (SimHost& sh : sims) {
+    set_mom_tiling(sh.d, sh.march);
+    deep += (long long)sh.d.mtiles_x * sh.d.mtiles_y * ((sh.d.nz + 23) / 24);
+  }
+  if (!alone && sims.size() > 1 && deep >= 4 * 1536) {
+    for (SimHost& sh : sims)
+      if (sh.march == 0) set_mom_tiling(sh.d, 24);
+    return;
+  }
+  int cap = 12;  // the largest of set_mom_tiling's defaults
+  auto blocks = [&]() {
+    long long n = 0;
+    for (const SimHost& sh : sims)
+      n += mom_blocks(sh.d, sh.march ? sh.march : std::min(cap, sh.d.mkz));
+    return n;
+  };
+  while (cap > 1 && blocks() < MARCH_MIN_BLOCKS) --cap;
+  for (SimHost& sh : sims)
+    if (sh.march == 0) set_mom_tiling(sh.d, std::min(cap, sh.d.mkz));
+}
+static void default_marches(std::vector<SimHost>& sims) {
+  for (SimHost& sh : sims) {  // by itself first: what launches over it alone use
+    std::vector<SimHost> one(1, sh);
+    default_march(one, true);
+    sh.solo = one[0].d.mkz;
+  }
+  default_march(sims, false);
 }
 
 // open x ends, a tube or a textured wall: the interface kernel's general
@@ -405,12 +451,12 @@ static Batch batch_all(const lbm_ctx* c) {
     if (sh.d.mtile_lx != mlx) mlx = 0;
   }
   return Batch{c->d_tab, c->d_blk, c->d_mblk, c->d_pmap, (int)c->sims.size(), c->cur, c->rd,
-               general, open, mlx};
+               general, open, mlx, 0};
 }
 static Batch batch_one(const lbm_ctx* c, int si) {
   return Batch{c->d_tab + si, nullptr, nullptr, nullptr, 1, c->cur, c->rd,
                general_geometry(c->sims[si].cfg), c->sims[si].cfg.open_x,
-               c->sims[si].d.mtile_lx};
+               c->sims[si].d.mtile_lx, c->sims[si].solo};
 }
 
 // workspace tail holding the batch tables
@@ -689,17 +735,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
       if (hipStreamSynchronize(st) != hipSuccess) return fail(LBM_EHIP, "synchronise failed");
     }
   }
-  // a batch whose blocks fill the GPU several times over even at a depth of
-  // 24 planes marches 24 (each block re-reads its two halo planes once per 24
-  // planes, not per 6 or 12; measured on the ensemble of 256 boxes 48 to 96
-  // wide: 8.75 ms per step at the single-box depths, 8.54 at 12, 8.36 at 24)
-  if (ctx->sims.size() > 1) {
-    long long deep = 0;
-    for (const SimHost& sh : ctx->sims)
-      deep += (long long)sh.d.mtiles_x * sh.d.mtiles_y * ((sh.d.nz + 23) / 24);
-    if (deep >= 4 * 1536)
-      for (SimHost& sh : ctx->sims) set_mom_tiling(sh.d, 24);
-  }
+  default_marches(ctx->sims);
   // batch tables: simulation records, block prefix, particle rows
   ctx->storage = cfg[0].storage;
   if (int rc = upload_tables(ctx, off)) return fail(rc, ctx->msg);
@@ -744,7 +780,7 @@ static int step_once(lbm_ctx* ctx, int slot) {
   hipStream_t st = ctx->stream;
   const Batch b = batch_all(ctx);
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][0], st));
-  HIPCHK(ctx, launch_interface(b, ctx->nblk, ctx->mnblk, st));
+  HIPCHK(ctx, launch_interface(b, ctx->mnblk, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][1], st));
   HIPCHK(ctx, launch_fused(b, ctx->storage, ctx->nblk, 0, nullptr, nullptr, nullptr, nullptr, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][2], st));
@@ -895,7 +931,8 @@ int lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t* chosen) {
         if (c > 0 && c > 2 * d.nx) continue;  // over half the tile idle
         set_tile(d, c);
         HIPCHK(ctx, hipMemcpyAsync(ctx->d_tab + si, &d, sizeof(SimDev), hipMemcpyHostToDevice, st));
-        const Batch b1 = batch_one(ctx, si);
+        Batch b1 = batch_one(ctx, si);
+        b1.mkz = 0;  // the depth that steps march
         Batch a1 = b1;  // buffer indices after a step's swap
         a1.cur ^= 1;
         a1.rd ^= 1;
@@ -903,7 +940,7 @@ int lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t* chosen) {
         float ms = 0.f;
         for (int r = 0; r <= reps; ++r) {  // the first pass warms up
           if (r == 1) HIPCHK(ctx, hipEventRecord(e0, st));
-          HIPCHK(ctx, launch_interface(b1, nb, mom_blocks(d), st));
+          HIPCHK(ctx, launch_interface(b1, mom_blocks(d), st));
           HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, nullptr, nullptr, nullptr, nullptr, st));
           HIPCHK(ctx, launch_moments(a1, ctx->storage, nb, mom_blocks(d), MOM_STEP, st));
         }
@@ -957,7 +994,8 @@ int lbm_set_march(lbm_ctx* ctx, int32_t sim, int32_t planes) {
     (void)hipGraphExecDestroy(ctx->graph_exec);
     ctx->graph_exec = nullptr;
   }
-  set_mom_tiling(ctx->sims[sim].d, planes);
+  ctx->sims[sim].march = planes;
+  default_marches(ctx->sims);
   return upload_tables(ctx, 0);
 }
 
@@ -1144,7 +1182,7 @@ int lbm_fields2(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, 
     float* ou = scratch + 2 * N;
     float* oF = scratch + 5 * N;
     const Batch b1 = batch_one(ctx, sim);
-    HIPCHK(ctx, launch_interface(b1, sim_blocks(d), mom_blocks(d), ctx->stream));
+    HIPCHK(ctx, launch_interface(b1, mom_blocks(d, b1.mkz), ctx->stream));
     HIPCHK(ctx, launch_fused(b1, ctx->storage, sim_blocks(d), 1, orho, ou, ophi, oF, ctx->stream));
     if ((what & LBM_F_FORCE) && force)
       HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));

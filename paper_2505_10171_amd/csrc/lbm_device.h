@@ -180,9 +180,10 @@ struct SimDev {
   // per-node moments of a state, 2 planes of N: rho, then phi (rho0 and
   // solid_phi at solids); rp[rd ^ 1] belongs to the state in pops[cur], rp[rd]
   // to the state before it (the FP16 reference of pops[cur]).  FP32 storage
-  // keeps rho only where phi is not exactly +-1 and at the nodes next to solids
-  // once the state has collided: in a pure fluid it is the sum of the
-  // populations, which whoever needs it forms (node_density)
+  // keeps rho only where phi is not exactly +-1 and, once the state has collided,
+  // at the nodes next to solids (what else the plane holds may be of an older
+  // state): elsewhere it is the sum of the populations, which whoever needs it
+  // forms (node_density)
   float* rp[2];
   float* nrm;          // 4 planes of N: n_x, n_y, n_z (NaN at solids), |G| (-1 at solids)
   float2* curv;        // per node (CSF coefficient, solid-neighbour bits as float)
@@ -328,6 +329,7 @@ struct Batch {
   int general;  // some simulation has open x ends, a tube or a textured wall
   int open;     // some simulation has open x ends
   int mlx;      // log2 of the moments tiles' x width if every simulation has the same, else 0
+  int mkz;      // marching depth of this launch, 0: each simulation's own
 };
 
 // (simulation, block within it) of global block g, given the block prefix blk

@@ -164,15 +164,18 @@ __device__ __forceinline__ int xcd_tile(int lin, int nblk) {
 // A pure tile plane (TileKind) takes no sources and, in FP32, no populations:
 // its phi stays, and its density is not kept.
 constexpr int MOM_HALO = 66 * 6;  // largest tile plane grown by one: (64 + 2)(4 + 2)
-// LX: log2 of the tiles' x width when the launch fixes it (the tile's LDS
-// offsets are then immediates), 0 to read it from the simulation
+// LX: log2 of the tiles' x width (the tile's LDS offsets are then immediates)
+struct MomLds {
+  v4f ring[3][MOM_HALO];
+  uint8_t kinds[258];
+};
 template <int STORE, int LX>
-__global__ __launch_bounds__(256) void k_moments(Batch bt) {
+__device__ __forceinline__ void moments_block(const Batch& bt, const SimDev& s, const int2 sb,
+                                              MomLds& lds) {
   using IO = Codec<STORE>;
   using T = typename IO::T;
-  __shared__ v4f ring[3][MOM_HALO];
-  const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
-  const SimDev& s = bt.tab[sb.x];
+  auto& ring = lds.ring;
+  auto& kinds = lds.kinds;
   const int N = (int)s.N;
   const int nx = s.nx, ny = s.ny, nz = s.nz, P = nx * ny;
   if (sb.y == 0 && threadIdx.x == 0) s.counters[0] = 0u;  // fresh list consumed
@@ -182,11 +185,11 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
   const GLB float* __restrict__ RO = gp((const float*)s.rp[bt.rd]);
   GLB float* __restrict__ RN = gp(s.rp[bt.rd ^ 1]);
   GLB uint16_t* __restrict__ MASK = gp(s.mask);
-  const int tlx = LX > 0 ? LX : s.mtile_lx;
-  const int tx = 1 << tlx, ty = 256 >> tlx, HX = tx + 2, HY = ty + 2;
+  constexpr int tlx = LX, tx = 1 << tlx, ty = 256 >> tlx, HX = tx + 2, HY = ty + 2;
   const int bx = sb.y % s.mtiles_x, r = sb.y / s.mtiles_x;
-  const int by = r % s.mtiles_y, z0 = (r / s.mtiles_y) * s.mkz;
-  const int kz = min(s.mkz, nz - z0);
+  const int mkz = bt.mkz > 0 ? bt.mkz : s.mkz;
+  const int by = r % s.mtiles_y, z0 = (r / s.mtiles_y) * mkz;
+  const int kz = min(mkz, nz - z0);
   const int t = (int)threadIdx.x;
   const int lx = t & (tx - 1), ly = t >> tlx;
   const int gx = bx * tx + lx, gy = by * ty + ly;
@@ -213,7 +216,6 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
   auto zwrap = [&](int z) { return z < 0 ? z + nz : (z >= nz ? z - nz : z); };
   // the kinds of the block's tile planes (entry zz + 1; mixed ones bound by
   // pure ones below and above)
-  __shared__ uint8_t kinds[258];
   {
     const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
     if (t < 2) kinds[t * (kz + 1)] = KIND_PURE_A;
@@ -332,6 +334,22 @@ __global__ __launch_bounds__(256) void k_moments(Batch bt) {
     __syncthreads();
   }
   store_pending();
+}
+
+// W64: every simulation of the launch has 64-wide tiles; else the tile width
+// is the block's simulation's (an ensemble mixes them: one uniform branch per
+// block, against offsets computed from a width in a register, see k_interface)
+template <int STORE, bool W64>
+__global__ __launch_bounds__(256) void k_moments(Batch bt) {
+  __shared__ MomLds lds;
+  const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
+  const SimDev& s = bt.tab[sb.x];
+  if (W64 || s.mtile_lx == 6)
+    moments_block<STORE, 6>(bt, s, sb, lds);
+  else if (s.mtile_lx == 5)
+    moments_block<STORE, 5>(bt, s, sb, lds);
+  else
+    moments_block<STORE, 4>(bt, s, sb, lds);
 }
 
 // Between steps, after the mask changed with the populations in place (and
@@ -455,26 +473,32 @@ constexpr int IF_NRM = MOM_HALO;  // grown by one: (64 + 2)(4 + 2)
 // separate instance, so that the periodic box on a plane carries none of their
 // bookkeeping).
 // LX: as for the moments pass
-template <bool OPEN, int LX>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_interface(Batch bt) {
-  __shared__ float fring[4][IF_PHI];
+struct IfLds {
+  float fring[4][IF_PHI];
   // normals of three planes, one array per component (the curvature reads
   // only the components its stencil direction needs); |G| only where the
   // curvature needs it, at the tile's own nodes
-  __shared__ float nrx[3][IF_NRM], nry[3][IF_NRM], nrz[3][IF_NRM], nrg[3][256];
-  const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
-  const SimDev& s = bt.tab[sb.x];
+  float nrx[3][IF_NRM], nry[3][IF_NRM], nrz[3][IF_NRM], nrg[3][256];
+  uint32_t wcls[2][4];
+};
+template <bool OPEN, int LX>
+__device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s, const int2 sb,
+                                                IfLds& lds) {
+  auto& fring = lds.fring;
+  auto &nrx = lds.nrx, &nry = lds.nry, &nrz = lds.nrz;
+  auto& nrg = lds.nrg;
+  auto& wcls = lds.wcls;
   const int N = (int)s.N;
   const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd ^ 1]) + s.N;
   GLB float* __restrict__ NX = gp(s.nrm);
   GLB float* __restrict__ CUR = gp((float*)s.curv);
   const int nx = s.nx, ny = s.ny, nz = s.nz, P = nx * ny;
-  const int tlx = LX > 0 ? LX : s.mtile_lx;
-  const int tx = 1 << tlx, ty = 256 >> tlx;
-  const int FX = tx + 4, FY = ty + 4, HX = tx + 2, HY = ty + 2;
+  constexpr int tlx = LX, tx = 1 << tlx, ty = 256 >> tlx;
+  constexpr int FX = tx + 4, FY = ty + 4, HX = tx + 2, HY = ty + 2;
   const int bx = sb.y % s.mtiles_x, r = sb.y / s.mtiles_x;
-  const int by = r % s.mtiles_y, z0 = (r / s.mtiles_y) * s.mkz;
-  const int kz = min(s.mkz, nz - z0);
+  const int mkz = bt.mkz > 0 ? bt.mkz : s.mkz;
+  const int by = r % s.mtiles_y, z0 = (r / s.mtiles_y) * mkz;
+  const int kz = min(mkz, nz - z0);
   const int t = (int)threadIdx.x;
   const int lx = t & (tx - 1), ly = t >> tlx;
   const int gx = bx * tx + lx, gy = by * ty + ly;
@@ -633,7 +657,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   // node of any other phi, 8 a solid (or open-end) node; each wave's word into
   // wcls, to be combined behind a barrier (two buffers in turn: a pure plane
   // passes one barrier only)
-  __shared__ uint32_t wcls[2][4];
   auto classify = [&](const float* v, int shift) -> uint32_t {
     bool sd = false;
 #pragma unroll
@@ -730,13 +753,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
       if (all & 8u) {
         if (in) {
           const int n = gx + nx * (gy + ny * z);
-          const int c = (lx + 2) + FX * (ly + 2);
+          // (the index is hidden from the compiler, which would form the eighteen
+          // addresses outside the march and spill the curvature's registers)
+          int c = (lx + 2) + FX * (ly + 2);
+          asm volatile("" : "+v"(c));
           bits = 0x80000000u;
           if (!(fring[fslot(z)][c] > PHI_SOLID_TEST)) {
             bits = 0u;
-// (not unrolled: its eighteen addresses, hoisted, would spill the
-            // registers of the curvature)
-#pragma unroll 1
+#pragma unroll
             for (int i = 1; i < Q; ++i)
               bits |= fring[fslot(z + cz(i))][c + cx(i) + FX * cy(i)] > PHI_SOLID_TEST ? (1u << i) : 0u;
           }
@@ -831,6 +855,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
       CUR[2 * n + 1] = __uint_as_float(bits);
     }
   }
+}
+
+// W64: as for the moments pass
+template <bool OPEN, bool W64>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_interface(Batch bt) {
+  __shared__ IfLds lds;
+  const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
+  const SimDev& s = bt.tab[sb.x];
+  if (W64 || s.mtile_lx == 6)
+    interface_block<OPEN, 6>(bt, s, sb, lds);
+  else if (s.mtile_lx == 5)
+    interface_block<OPEN, 5>(bt, s, sb, lds);
+  else
+    interface_block<OPEN, 4>(bt, s, sb, lds);
 }
 
 // ------------------------------------------------------------- fused kernel
@@ -963,9 +1001,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     return;
   }
   if (!(rho > 0.f) || !(uu <= 0.09f)) atomicOr(&s.counters[1], (uint32_t)ST_UNSTABLE);
-  // next to a solid FP32 keeps the density of the colliding state for the link
-  // kernel
-  if (STORE == 0 && bits != 0u) gp(s.rp[bt.rd ^ 1])[n] = rho;
+  // next to a solid the density of the colliding state for the link kernel: the
+  // moments pass keeps none on a pure tile plane (one that is mixed now may
+  // have been pure then, but not around a node of another phi than +-1)
+  if (STORE == 0 && bits != 0u && phi_pure(phi)) gp(s.rp[bt.rd ^ 1])[n] = rho;
   // local relaxation: harmonic mean of the kinematic viscosities
   const float inv_nu = (1.0f + phi) * s.inv2nua + (1.0f - phi) * s.inv2nub;
   const float om = 1.0f / (0.5f + 3.0f / inv_nu);
@@ -1159,20 +1198,19 @@ static inline unsigned nblocks(long long n, int b) { return (unsigned)((n + b - 
 // Batched launchers: one launch over every simulation of the batch.
 // nblk: total 256-node blocks; np_rows: total particle rows; Bmax: the largest
 // mask-box side of the batch.
-// nblk: per-node blocks; mnblk: blocks of the moments tiling (k_interface)
-hipError_t launch_interface(const Batch& b, unsigned nblk, unsigned mnblk, hipStream_t st) {
-  (void)nblk;
-  const bool w64 = b.mlx == 6;  // 64-wide tiles: the instance with them fixed
+// mnblk: blocks of the moments tiling
+hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
+  const dim3 g(mnblk), t(256);
   if (b.general) {
-    if (w64)
-      hipLaunchKernelGGL((k_interface<true, 6>), dim3(mnblk), dim3(256), 0, st, b);
+    if (b.mlx == 6)
+      hipLaunchKernelGGL((k_interface<true, true>), g, t, 0, st, b);
     else
-      hipLaunchKernelGGL((k_interface<true, 0>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_interface<true, false>), g, t, 0, st, b);
   } else {
-    if (w64)
-      hipLaunchKernelGGL((k_interface<false, 6>), dim3(mnblk), dim3(256), 0, st, b);
+    if (b.mlx == 6)
+      hipLaunchKernelGGL((k_interface<false, true>), g, t, 0, st, b);
     else
-      hipLaunchKernelGGL((k_interface<false, 0>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_interface<false, false>), g, t, 0, st, b);
   }
   return hipGetLastError();
 }
@@ -1221,15 +1259,16 @@ hipError_t launch_moments(const Batch& b, int storage, unsigned nblk, unsigned m
                           hipStream_t st) {
   if (mode == MOM_BOUNDARY)
     hipLaunchKernelGGL(k_moments_boundary, dim3(nblk), dim3(256), 0, st, b);
-  else if (b.mlx == 6) {
-    if (storage == 0)
-      hipLaunchKernelGGL((k_moments<0, 6>), dim3(mnblk), dim3(256), 0, st, b);
+  else if (storage == 0) {
+    if (b.mlx == 6)
+      hipLaunchKernelGGL((k_moments<0, true>), dim3(mnblk), dim3(256), 0, st, b);
     else
-      hipLaunchKernelGGL((k_moments<1, 6>), dim3(mnblk), dim3(256), 0, st, b);
-  } else if (storage == 0) {
-    hipLaunchKernelGGL((k_moments<0, 0>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_moments<0, false>), dim3(mnblk), dim3(256), 0, st, b);
   } else {
-    hipLaunchKernelGGL((k_moments<1, 0>), dim3(mnblk), dim3(256), 0, st, b);
+    if (b.mlx == 6)
+      hipLaunchKernelGGL((k_moments<1, true>), dim3(mnblk), dim3(256), 0, st, b);
+    else
+      hipLaunchKernelGGL((k_moments<1, false>), dim3(mnblk), dim3(256), 0, st, b);
   }
   return hipGetLastError();
 }
