@@ -5,7 +5,7 @@
 //   k_fused (collide + recolour + stream + bounce-back + momentum exchange)
 //   k_capbox, k_capillary (capillary force)      -- if the sim has particles
 //   k_dem (contacts, friction, Verlet sub-steps)
-//   k_claim, k_release, k_cover (solid mask of the new positions)
+//   k_mask (solid mask of the new positions)
 //   k_refill (fresh fluid nodes)
 //   k_moments (order parameter of the new state)
 // No device memory is allocated and nothing is synchronised inside lbm_step.
@@ -87,7 +87,7 @@ struct SimLayout {
   long long N;
   int np, Bmask, Bcap, hist_cap;
   size_t pop_bytes, fresh_cap;
-  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_claim, off_fresh, off_fresh_own,
+  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_fresh, off_fresh_own,
       off_counters, off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_caporg, off_mass,
       off_step;
   size_t total;
@@ -200,7 +200,7 @@ SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
     L.off_kind = take((size_t)t.mtiles_x * t.mtiles_y * t.nz);
   }
   L.off_mask = take(2 * L.N);
-  L.off_claim = take(4 * L.N);
+  (void)take(4 * L.N);  // unused: callers rely on 46 bytes per node besides the populations
   L.off_fresh = take(4 * L.fresh_cap);
   L.off_fresh_own = take(4 * L.fresh_cap);
   L.off_counters = take(64);
@@ -664,7 +664,6 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     d.curv = (float2*)(b + sh.L.off_cur);
     d.kind = (uint8_t*)(b + sh.L.off_kind);
     d.mask = (uint16_t*)(b + sh.L.off_mask);
-    d.claim = (uint32_t*)(b + sh.L.off_claim);
     d.fresh = (uint32_t*)(b + sh.L.off_fresh);
     d.fresh_own = (uint32_t*)(b + sh.L.off_fresh_own);
     d.counters = (uint32_t*)(b + sh.L.off_counters);

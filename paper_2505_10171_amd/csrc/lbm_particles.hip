@@ -42,94 +42,104 @@ __device__ __attribute__((noinline)) bool inside_sphere(int x, int y, int z, con
   return d2 < R * R;
 }
 
-// claim: lowest particle index inside which a node lies (new positions)
-__global__ void k_claim(Batch bt) {
+// Mask of the new positions, one grid row of blocks per particle p.  A node's new
+// owner is the lowest particle inside which it lies.  With RELEASE, the nodes
+// that belonged to p (old box) pass to their new owner or become fluid (fresh);
+// the fluid nodes of the new box whose owner is p become p's.  Every node is
+// written by one block only: by its old owner's, or, if it was fluid, by its new
+// owner's; what another block may read there meanwhile (the new code, or the
+// fresh mark) leaves that block's part unchanged, so the pass needs no claims in
+// memory and no second and third kernel (one launch for three: 12 -> 5 us
+// with one sphere of radius 4, 14 -> 6.6 with 20 of radius 5, 39 -> 33 with 500
+// of radius 4, whose blocks each look through all of them).
+constexpr int MASK_NEAR = 64;  // overlapping particles listed; more: all are tested
+template <bool RELEASE>
+__global__ __launch_bounds__(256) void k_mask(Batch bt) {
   const int2 sp = batch_particle(bt, blockIdx.y);
   const SimDev& s = bt.tab[sp.x];
-  const int p = sp.y;
-  const DevParticle& P = s.P[p];
-  const Box b = particle_box(s, P.x, P.R);
-  const int vol = b.w[0] * b.w[1] * b.w[2];
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
-    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
-    const int x = wrapi(b.lo[0] + ix, s.nx), y = wrapi(b.lo[1] + iy, s.ny),
-              z = wrapi(b.lo[2] + iz, s.nz);
-    if (static_wall(s, x, y, z)) continue;
-    if (inside_sphere(x, y, z, P.x, P.R, s.nx, s.ny, s.nz)) {
-      const long long n = (long long)x + (long long)s.nx * ((long long)y + (long long)s.ny * z);
-      atomicMin(&s.claim[n], (uint32_t)p);
-    }
-  }
-}
-
-// release: nodes that belonged to p (old box) become fluid (fresh) or pass to
-// the particle that claims them now.  Each such node is visited once (by p).
-__global__ void k_release(Batch bt) {
-  const int2 sp = batch_particle(bt, blockIdx.y);
-  const SimDev& s = bt.tab[sp.x];
-  const int p = sp.y;
-  const DevParticle& P = s.P[p];
-  double Xo[3] = {P.xo[0], P.xo[1], P.xo[2]};
-  const Box b = particle_box(s, Xo, P.Ro);
-  const int vol = b.w[0] * b.w[1] * b.w[2];
+  const int p = sp.y, np = s.np;
+  const DevParticle* PP = s.P;
   // the record's fields held in registers (the stores below may alias it)
   const int nx = s.nx, ny = s.ny, nz = s.nz;
+  const double X[3] = {PP[p].x[0], PP[p].x[1], PP[p].x[2]}, R = PP[p].R;
+  const double Xo[3] = {PP[p].xo[0], PP[p].xo[1], PP[p].xo[2]}, Ro = PP[p].Ro;
   GLB uint16_t* __restrict__ MASK = gp(s.mask);
-  const GLB uint32_t* __restrict__ CLAIM = gp((const uint32_t*)s.claim);
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
-    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
-    const int x = wrapi(b.lo[0] + ix, nx), y = wrapi(b.lo[1] + iy, ny), z = wrapi(b.lo[2] + iz, nz);
-    const unsigned n = (unsigned)(x + nx * (y + ny * z));
-    // mask and claim in one round trip
-    const uint16_t m = at((const GLB uint16_t*)MASK, n);
-    const uint32_t c = at(CLAIM, n);
-    const bool mine = m == (uint16_t)(2 + p);
-    const bool fresh = mine && c == 0xFFFFFFFFu;
+  // a node's mask code, of both boxes, with the candidates' positions in flight
+  const Box b = particle_box(s, X, R), bo = particle_box(s, Xo, Ro);
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  auto node = [&](const Box& q, int& x, int& y, int& z) -> bool {
+    if (k >= q.w[0] * q.w[1] * q.w[2]) return false;
+    x = wrapi(q.lo[0] + k % q.w[0], nx);
+    y = wrapi(q.lo[1] + (k / q.w[0]) % q.w[1], ny);
+    z = wrapi(q.lo[2] + k / (q.w[0] * q.w[1]), nz);
+    return true;
+  };
+  int x, y, z, xo = 0, yo = 0, zo = 0;
+  const bool in = node(b, x, y, z), ino = RELEASE && node(bo, xo, yo, zo);
+  const unsigned n = in ? (unsigned)(x + nx * (y + ny * z)) : 0u;
+  const unsigned no = ino ? (unsigned)(xo + nx * (yo + ny * zo)) : 0u;
+  const uint16_t m = at((const GLB uint16_t*)MASK, n);
+  const uint16_t mo = RELEASE ? at((const GLB uint16_t*)MASK, no) : (uint16_t)0;
+  // particles whose new sphere meets p's new or old one: a node inside both
+  // spheres is nearer than both radii to both centres (the margin covers rounding)
+  __shared__ int near[MASK_NEAR], n_near;
+  if (threadIdx.x == 0) n_near = 0;
+  __syncthreads();
+  for (int q = threadIdx.x; q < np; q += blockDim.x) {
+    if (q == p) continue;
+    const double Xq[3] = {PP[q].x[0], PP[q].x[1], PP[q].x[2]}, Rq = PP[q].R;
+    auto meets = [&](const double* C, double Rc) {
+      const double dx = wrapd(Xq[0] - C[0], (double)nx), dy = wrapd(Xq[1] - C[1], (double)ny),
+                   dz = wrapd(Xq[2] - C[2], (double)nz);
+      const double lim = Rq + Rc + 1e-3;
+      return dx * dx + dy * dy + dz * dz < lim * lim;
+    };
+    if (meets(X, R) || (RELEASE && meets(Xo, Ro))) {
+      const int slot = atomicAdd(&n_near, 1);
+      if (slot < MASK_NEAR) near[slot] = q;
+    }
+  }
+  __syncthreads();
+  const bool listed = n_near <= MASK_NEAR;
+  const int tests = listed ? n_near : np;
+  // the lowest particle that holds node (x, y, z), np if none
+  auto owner = [&](int x, int y, int z) {
+    int c = inside_sphere(x, y, z, X, R, nx, ny, nz) ? p : np;
+    for (int u = 0; u < tests; ++u) {
+      const int q = listed ? near[u] : u;
+      if (q < c && q != p) {
+        const double Xq[3] = {PP[q].x[0], PP[q].x[1], PP[q].x[2]};
+        if (inside_sphere(x, y, z, Xq, PP[q].R, nx, ny, nz)) c = q;
+      }
+    }
+    return c;
+  };
+  if (RELEASE) {
+    const bool mine = ino && mo == (uint16_t)(2 + p);
+    const int c = mine ? owner(xo, yo, zo) : p;
+    const bool fresh = c == np;
     // the wave's fresh nodes take consecutive slots of the fresh list: one
     // atomic per wave (the list's order does not matter to the refill)
     const unsigned long long want = __ballot(fresh);
-    uint32_t base0 = 0;
-    const int lane = (int)(threadIdx.x & 63);
-    const int first = want ? __ffsll((long long)want) - 1 : 0;
-    if (want && lane == first) base0 = atomicAdd(&s.counters[0], (uint32_t)__popcll(want));
-    base0 = (uint32_t)__shfl((int)base0, first, 64);
-    if (!mine) continue;
-    if (fresh) {
-      MASK[n] = FRESH_BIT;
-      const uint32_t slot = base0 + (uint32_t)__popcll(want & ((1ull << lane) - 1ull));
-      if (slot < s.fresh_cap) {
-        s.fresh[slot] = n;
-        s.fresh_own[slot] = (uint32_t)p;
-      } else {
-        atomicOr(&s.counters[1], (uint32_t)ST_FRESH_FULL);
+    if (want) {
+      const int lane = (int)(threadIdx.x & 63), first = __ffsll((long long)want) - 1;
+      uint32_t base0 = 0;
+      if (lane == first) base0 = atomicAdd(&s.counters[0], (uint32_t)__popcll(want));
+      base0 = (uint32_t)__shfl((int)base0, first, 64);
+      if (fresh) {
+        MASK[no] = FRESH_BIT;
+        const uint32_t slot = base0 + (uint32_t)__popcll(want & ((1ull << lane) - 1ull));
+        if (slot < s.fresh_cap) {
+          s.fresh[slot] = no;
+          s.fresh_own[slot] = (uint32_t)p;
+        } else {
+          atomicOr(&s.counters[1], (uint32_t)ST_FRESH_FULL);
+        }
       }
-    } else if (c != (uint32_t)p) {
-      MASK[n] = (uint16_t)(2 + c);
     }
+    if (mine && !fresh && c != p) MASK[no] = (uint16_t)(2 + c);
   }
-}
-
-// cover: nodes claimed by p become p's solid nodes; claims are cleared
-__global__ void k_cover(Batch bt) {
-  const int2 sp = batch_particle(bt, blockIdx.y);
-  const SimDev& s = bt.tab[sp.x];
-  const int p = sp.y;
-  const DevParticle& P = s.P[p];
-  const Box b = particle_box(s, P.x, P.R);
-  const int vol = b.w[0] * b.w[1] * b.w[2];
-  // the record's fields held in registers (the stores below may alias it)
-  const int nx = s.nx, ny = s.ny, nz = s.nz;
-  GLB uint16_t* __restrict__ MASK = gp(s.mask);
-  GLB uint32_t* __restrict__ CLAIM = gp(s.claim);
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
-    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
-    const int x = wrapi(b.lo[0] + ix, nx), y = wrapi(b.lo[1] + iy, ny), z = wrapi(b.lo[2] + iz, nz);
-    const unsigned n = (unsigned)(x + nx * (y + ny * z));
-    if (at((const GLB uint32_t*)CLAIM, n) == (uint32_t)p) {
-      MASK[n] = (uint16_t)(2 + p);
-      CLAIM[n] = 0xFFFFFFFFu;
-    }
-  }
+  if (in && m == 0 && owner(x, y, z) == p) MASK[n] = (uint16_t)(2 + p);
 }
 
 // Refilling (refilling eqs.): f_a, f_b of a fresh node = equilibria of the mean
@@ -1252,9 +1262,10 @@ hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_r
                               hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
   dim3 grid(box_blocks(Bmax), np_rows);
-  hipLaunchKernelGGL(k_claim, grid, dim3(256), 0, st, b);
-  if (with_release) hipLaunchKernelGGL(k_release, grid, dim3(256), 0, st, b);
-  hipLaunchKernelGGL(k_cover, grid, dim3(256), 0, st, b);
+  if (with_release)
+    hipLaunchKernelGGL(k_mask<true>, grid, dim3(256), 0, st, b);
+  else
+    hipLaunchKernelGGL(k_mask<false>, grid, dim3(256), 0, st, b);
   return hipGetLastError();
 }
 
