@@ -3,11 +3,11 @@
 // The context carves the caller's device workspace, uploads the initial state,
 // and issues the per-step kernel sequence on the caller's stream:
 //   k_fused (collide + recolour + stream + bounce-back + momentum exchange)
-//   k_capbox, k_capillary (capillary force)      -- if the sim has particles
+//   k_links (moving walls, momentum exchange, capillary boxes) and k_capillary
+//   (capillary force)                            -- if the sim has particles
 //   k_dem (contacts, friction, Verlet sub-steps)
 //   k_mask (solid mask of the new positions)
-//   k_refill (fresh fluid nodes)
-//   k_moments (order parameter of the new state)
+//   k_moments (fresh fluid nodes refilled, order parameter of the new state)
 // No device memory is allocated and nothing is synchronised inside lbm_step.
 #include <math.h>
 #include <stdarg.h>
@@ -28,9 +28,12 @@ namespace lbm {
 hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st);
 hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int mode, float* orho,
                         float* ou, float* ophi, float* oF, hipStream_t st);
-hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, hipStream_t st);
-hipError_t launch_moments(const Batch& b, int storage, unsigned nblk, unsigned mnblk, int mode,
-                          hipStream_t st);
+hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, bool cap,
+                        hipStream_t st);
+hipError_t launch_moments(const Batch& b, int storage, unsigned mnblk, size_t fresh_cap_max,
+                          int np_max, hipStream_t st);
+hipError_t launch_boundary(const Batch& b, int storage, unsigned nblk, size_t fresh_cap_max,
+                           int np_max, hipStream_t st);
 hipError_t launch_init_mask(const SimDev& s, hipStream_t st);
 hipError_t launch_init_pops(const SimDev& s, void* pops, hipStream_t st);
 hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, double* acc,
@@ -38,11 +41,7 @@ hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, doubl
 hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
 hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
                               hipStream_t st);
-hipError_t launch_refill(const Batch& b, int storage, size_t fresh_cap_max, int np_max, int mode,
-                         hipStream_t st);
-// kernel modes (lbm_fluid.hip, lbm_particles.hip): in a step, or between steps
-constexpr int MOM_STEP = 0, MOM_BOUNDARY = 1, REFILL_STEP = 0, REFILL_BOUNDARY = 1;
-hipError_t launch_capillary(const Batch& b, int np_rows, int cap_B, int npts, hipStream_t st);
+hipError_t launch_capillary(const Batch& b, int np_rows, int npts, hipStream_t st);
 hipError_t launch_dem(const Batch& b, int np_max, int np_rows, int n_sub_max, hipStream_t st);
 }  // namespace lbm
 
@@ -88,7 +87,7 @@ struct SimLayout {
   int np, Bmask, Bcap, hist_cap;
   size_t pop_bytes, fresh_cap;
   size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_fresh, off_fresh_own,
-      off_counters, off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_caporg, off_mass,
+      off_counters, off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_mass,
       off_step;
   size_t total;
 };
@@ -210,7 +209,6 @@ SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
   L.off_view = take(sizeof(DemView) * 2 * (size_t)L.np);
   L.off_hist = take(sizeof(double) * (size_t)L.hist_cap * L.np * LBM_HIST_DOUBLES);
   L.off_capbox = take(sizeof(float4) * (size_t)L.np * L.Bcap * L.Bcap * L.Bcap);
-  L.off_caporg = take(sizeof(int) * 3 * (size_t)L.np);
   L.off_mass = take(2 * sizeof(double));
   L.off_step = take(sizeof(unsigned long long));
   L.total = o;
@@ -320,7 +318,7 @@ struct lbm_ctx {
   uint32_t* d_mblk = nullptr;
   int2* d_pmap = nullptr;
   unsigned nblk = 0;
-  int np_rows = 0, np_max = 0, Bmax = 0, cap_B = 0, npts = 0, n_sub_max = 1;
+  int np_rows = 0, np_max = 0, Bmax = 0, npts = 0, n_sub_max = 1;
   bool cap_needed = false;  // some simulation with particles has a capillary force
   size_t fresh_cap_max = 0;
   unsigned mnblk = 0;  // blocks of the moments pass over the batch
@@ -451,12 +449,12 @@ static Batch batch_all(const lbm_ctx* c) {
     if (sh.d.mtile_lx != mlx) mlx = 0;
   }
   return Batch{c->d_tab, c->d_blk, c->d_mblk, c->d_pmap, (int)c->sims.size(), c->cur, c->rd,
-               general, open, mlx, 0};
+               general, open, mlx, 0, 0};
 }
 static Batch batch_one(const lbm_ctx* c, int si) {
   return Batch{c->d_tab + si, nullptr, nullptr, nullptr, 1, c->cur, c->rd,
                general_geometry(c->sims[si].cfg), c->sims[si].cfg.open_x,
-               c->sims[si].d.mtile_lx, c->sims[si].solo};
+               c->sims[si].d.mtile_lx, c->sims[si].solo, 0};
 }
 
 // workspace tail holding the batch tables
@@ -502,7 +500,7 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
   std::vector<SimDev> tab(n_sims);
   std::vector<uint32_t> blk(n_sims + 1, 0), mblk(n_sims + 1, 0);
   std::vector<int2> pmap;
-  ctx->np_max = ctx->Bmax = ctx->cap_B = ctx->npts = 0;
+  ctx->np_max = ctx->Bmax = ctx->npts = 0;
   ctx->cap_needed = false;
   ctx->n_sub_max = 1;
   ctx->fresh_cap_max = 0;
@@ -520,7 +518,6 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
     if (sh.d.np > 0) ctx->n_sub_max = std::max(ctx->n_sub_max, sh.d.n_sub);
     if (sh.d.np > 0) {
       ctx->Bmax = std::max(ctx->Bmax, sh.L.Bmask);
-      ctx->cap_B = std::max(ctx->cap_B, sh.d.cap_B);
       ctx->npts = std::max(ctx->npts, sh.d.cap_na * sh.d.cap_nphi);
       ctx->cap_needed |= sh.d.cap_pref != 0.0;
       ctx->fresh_cap_max = std::max(ctx->fresh_cap_max, (size_t)sh.d.fresh_cap);
@@ -544,12 +541,11 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
 static int post_dem_pipeline(lbm_ctx* ctx, int si, bool with_release) {
   const SimHost& sh = ctx->sims[si];
   const SimDev& s = sh.d;
-  const Batch b = batch_one(ctx, si);
-  if (s.np > 0) {
+  Batch b = batch_one(ctx, si);
+  b.fc = 2;
+  if (s.np > 0)
     HIPCHK(ctx, launch_mask_update(b, s.np, sh.L.Bmask, with_release, ctx->stream));
-    HIPCHK(ctx, launch_refill(b, ctx->storage, s.fresh_cap, s.np, REFILL_BOUNDARY, ctx->stream));
-  }
-  HIPCHK(ctx, launch_moments(b, ctx->storage, sim_blocks(s), 0, MOM_BOUNDARY, ctx->stream));
+  HIPCHK(ctx, launch_boundary(b, ctx->storage, sim_blocks(s), s.fresh_cap, s.np, ctx->stream));
   return LBM_OK;
 }
 
@@ -688,7 +684,6 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     d.cap_nphi = (int)llround(360.0 / c.cap_dang_deg);
     d.cap_B = sh.L.Bcap;
     d.capbox = (float4*)(b + sh.L.off_capbox);
-    d.capbox_org = (int*)(b + sh.L.off_caporg);
     d.mass_acc = (double*)(b + sh.L.off_mass);
     d.step_counter = (unsigned long long*)(b + sh.L.off_step);
 
@@ -783,7 +778,7 @@ static int step_once(lbm_ctx* ctx, int slot) {
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][1], st));
   HIPCHK(ctx, launch_fused(b, ctx->storage, ctx->nblk, 0, nullptr, nullptr, nullptr, nullptr, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][2], st));
-  HIPCHK(ctx, launch_links(b, ctx->storage, ctx->np_rows, ctx->Bmax, st));
+  HIPCHK(ctx, launch_links(b, ctx->storage, ctx->np_rows, ctx->Bmax, ctx->cap_needed, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][3], st));
   ctx->cur ^= 1;
   ctx->rd ^= 1;
@@ -791,13 +786,12 @@ static int step_once(lbm_ctx* ctx, int slot) {
   if (ctx->np_rows > 0) {
     // without surface tension (sigma = 0) the capillary force is zero: the DEM
     // reads the accumulators it cleared itself
-    if (ctx->cap_needed) HIPCHK(ctx, launch_capillary(a, ctx->np_rows, ctx->cap_B, ctx->npts, st));
+    if (ctx->cap_needed) HIPCHK(ctx, launch_capillary(a, ctx->np_rows, ctx->npts, st));
     HIPCHK(ctx, launch_dem(a, ctx->np_max, ctx->np_rows, ctx->n_sub_max, st));
     HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->Bmax, true, st));
-    HIPCHK(ctx, launch_refill(a, ctx->storage, ctx->fresh_cap_max, ctx->np_max, REFILL_STEP, st));
   }
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][4], st));
-  HIPCHK(ctx, launch_moments(a, ctx->storage, ctx->nblk, ctx->mnblk, MOM_STEP, st));
+  HIPCHK(ctx, launch_moments(a, ctx->storage, ctx->mnblk, ctx->fresh_cap_max, ctx->np_max, st));
   if (slot >= 0) {
     HIPCHK(ctx, hipEventRecord(P.ev[slot][5], st));
     P.pending[slot] = true;
@@ -941,7 +935,7 @@ int lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t* chosen) {
           if (r == 1) HIPCHK(ctx, hipEventRecord(e0, st));
           HIPCHK(ctx, launch_interface(b1, mom_blocks(d), st));
           HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, nullptr, nullptr, nullptr, nullptr, st));
-          HIPCHK(ctx, launch_moments(a1, ctx->storage, nb, mom_blocks(d), MOM_STEP, st));
+          HIPCHK(ctx, launch_moments(a1, ctx->storage, mom_blocks(d), 0, 0, st));
         }
         HIPCHK(ctx, hipEventRecord(e1, st));
         HIPCHK(ctx, hipEventSynchronize(e1));

@@ -193,7 +193,7 @@ struct SimDev {
   uint16_t* mask;      // 0 fluid, 1 wall, 2+p particle p; FRESH_BIT while refilling
   uint32_t* fresh;     // fresh-node list: node index
   uint32_t* fresh_own; // fresh-node list: particle that uncovered it
-  uint32_t* counters;  // [0] fresh count, [1] status flags, [2] fresh overflow
+  uint32_t* counters;  // [0] fresh count of a step, [1] status flags, [2] fresh count between steps
   uint32_t fresh_cap;
   // particles
   DevParticle* P;
@@ -209,7 +209,6 @@ struct SimDev {
   int cap_na, cap_nphi;
   int cap_B;           // side of the per-particle capillary box
   float4* capbox;      // np * B^3: (phi, Gx, Gy, Gz); phi = 2 marks a solid corner
-  int* capbox_org;     // np * 3 box origins
   double* mass_acc;    // 2 doubles
   unsigned long long* step_counter;
   // node blocks of the per-node kernels (256 threads): tile_x = 0 runs 256
@@ -329,6 +328,9 @@ struct Batch {
   int open;     // some simulation has open x ends
   int mlx;      // log2 of the moments tiles' x width if every simulation has the same, else 0
   int mkz;      // marching depth of this launch, 0: each simulation's own
+  // the counter of the fresh list: 0 in a step (emptied by the next DEM, as the
+  // refill shares a launch with the moments pass), 2 between steps
+  int fc;
 };
 
 // (simulation, block within it) of global block g, given the block prefix blk

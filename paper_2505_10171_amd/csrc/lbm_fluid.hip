@@ -14,6 +14,8 @@
 // bounce-back of f, one thread per node, reading and writing every population
 // exactly once), k_links (moving-wall terms and momentum exchange at particle
 // links) and k_moments (density and order parameter of the post-stream state).
+#include <algorithm>
+
 #include "lbm_device.h"
 
 namespace lbm {
@@ -149,13 +151,129 @@ __device__ __forceinline__ int xcd_tile(int lin, int nblk) {
   return lin;
 }
 
+// ---------------------------------------------------------------- refill
+// Refilling (refilling eqs.): f_a, f_b of a fresh node = equilibria of the mean
+// neighbour densities (fluid, not fresh, D3Q19 neighbours; rho0/2 each if none)
+// at the surface velocity of the particle that uncovered it.  Stored are the
+// total f and the node's moments (rho, phi) in rp[rd ^ 1].  The neighbour
+// densities are those of the post-stream state: in a step (REFILL_STEP) rebuilt
+// from the state that collided, as the moments pass does; between steps
+// (REFILL_BOUNDARY) the current moments rp[rd ^ 1].  In a step the refill's blocks
+// run in the launch of the moments pass: neither reads what the other writes (the
+// moments pass leaves fresh nodes alone), and the refill's dependent loads hide
+// behind it (500 spheres 23 us, 20 spheres 9 to 12, one 2 to 4).
+enum { REFILL_STEP = 0, REFILL_BOUNDARY = 1 };
+constexpr int REFILL_PER = 14;  // fresh nodes per block: a thread per neighbour direction
+struct RefillLds {
+  float a[REFILL_PER][18], b[REFILL_PER][18];
+  int c[REFILL_PER][18];
+};
+// block `block` of the `blocks` that refill simulation s
+template <int STORE, int MODE>
+__device__ __forceinline__ void refill_block(const Batch& bt, const SimDev& s, int block,
+                                             int blocks, RefillLds& lds) {
+  using IO = Codec<STORE>;
+  using T = typename IO::T;
+  if (s.np == 0) return;
+  T* b = (T*)s.pops[bt.cur];
+  const GLB float* RO = gp((const float*)s.rp[bt.rd]);
+  float* RN = s.rp[bt.rd ^ 1];
+  constexpr int PER = REFILL_PER;
+  auto &sh_a = lds.a, &sh_b = lds.b;
+  auto& sh_c = lds.c;
+  const uint32_t cnt = min(s.counters[bt.fc], s.fresh_cap);
+  const int N = (int)s.N;
+  const int slot = threadIdx.x / 18, dir = threadIdx.x % 18 + 1;
+  for (uint32_t base = (uint32_t)block * PER; base < cnt; base += (uint32_t)blocks * PER) {
+    const uint32_t k = base + slot;
+    if (slot < PER) {
+      float ra = 0.f, rb = 0.f;
+      int c = 0;
+      if (k < cnt) {
+        const int n = (int)s.fresh[k];
+        const int x = n % s.nx, y = (n / s.nx) % s.ny, z = n / (s.nx * s.ny);
+        const int mx = wrapi(x + cx(dir), s.nx), my = wrapi(y + cy(dir), s.ny),
+                  mz = wrapi(z + cz(dir), s.nz);
+        const int m = mx + s.nx * (my + s.ny * mz);
+        // a fluid node that is not fresh: in a step, one that was fluid in the
+        // state that collided (the moments pass beside it clears the marks)
+        const uint16_t mk = s.mask[m];
+        if (MODE == REFILL_STEP ? (mk & ~FRESH_BIT) == 0 && !(RO[N + m] > PHI_SOLID_TEST)
+                                : mk == 0) {
+          float rho, sg;
+          if (MODE == REFILL_STEP) {
+            const Nbr nbm(mx, my, mz, s.nx, s.ny, s.nz);
+            rebuild_moments<STORE>(gp((const T*)b), RO, gp((const float*)s.nrm), N, m, nbm,
+                                   s.rho0, 0.5f * s.beta, STORE ? RO[m] : 0.f, rho, sg);
+          } else {
+            // FP32 keeps no density where phi is +-1
+            const float ph = RN[N + m];
+            rho = STORE == 0 && phi_pure(ph)
+                      ? node_density<STORE>(gp((const T*)b), N, m, s.rho0, 0.f)
+                      : RN[m];
+            sg = rho * ph;
+          }
+          ra = 0.5f * (rho + sg);
+          rb = 0.5f * (rho - sg);
+          c = 1;
+        }
+      }
+      sh_a[slot][dir - 1] = ra;
+      sh_b[slot][dir - 1] = rb;
+      sh_c[slot][dir - 1] = c;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < PER && base + threadIdx.x < cnt) {
+      const uint32_t kk = base + threadIdx.x;
+      float sa = 0.f, sb = 0.f;
+      int c = 0;
+      for (int i = 0; i < 18; ++i) {
+        sa += sh_a[threadIdx.x][i];
+        sb += sh_b[threadIdx.x][i];
+        c += sh_c[threadIdx.x][i];
+      }
+      const int n = (int)s.fresh[kk];
+      const int p = (int)s.fresh_own[kk];
+      const int x = n % s.nx, y = (n / s.nx) % s.ny, z = n / (s.nx * s.ny);
+      const float ra = c ? sa / c : 0.5f * s.rho0;
+      const float rb = c ? sb / c : 0.5f * s.rho0;
+      const DevParticle& P = s.P[p];
+      const double rx = wrapd((double)x - P.x[0], (double)s.nx);
+      const double ry = wrapd((double)y - P.x[1], (double)s.ny);
+      const double rz = wrapd((double)z - P.x[2], (double)s.nz);
+      const float ux = (float)(P.v[0] + P.w[1] * rz - P.w[2] * ry);
+      const float uy = (float)(P.v[1] + P.w[2] * rx - P.w[0] * rz);
+      const float uz = (float)(P.v[2] + P.w[0] * ry - P.w[1] * rx);
+      const float uu = ux * ux + uy * uy + uz * uz;
+      const float rho = ra + rb;
+      // FP16: encoded with the reference the decoders of this state use
+      const float Rn = STORE ? RO[n] : 0.f;
+      for (int q = 0; q < Q; ++q) {
+        const float cu = cx(q) * ux + cy(q) * uy + cz(q) * uz;
+        const float poly = 3.0f * cu + 4.5f * cu * cu - 1.5f * uu;
+        const float dq = wq(q) * ((rho - s.rho0) + rho * poly);
+        IO::st(b + pidx(q, N, n), wq(q) * s.rho0, 1.0f / (wq(q) * s.rho0), wq(q) * Rn, dq);
+      }
+      // f^a - f^b = (ra - rb) / rho f: the order parameter of the node
+      RN[n] = rho;
+      RN[N + n] = (ra - rb) / rho;
+    }
+    __syncthreads();
+  }
+}
+
+template <int STORE>
+__global__ __launch_bounds__(256) void k_refill_boundary(Batch bt) {
+  __shared__ RefillLds lds;
+  refill_block<STORE, REFILL_BOUNDARY>(bt, bt.tab[blockIdx.y], blockIdx.x, gridDim.x, lds);
+}
+
 // ------------------------------------------------------------- moments kernel
 // Density and order parameter phi = sum g / rho (order-parameter eq.) of every
 // fluid node of the post-stream state into rp[rd ^ 1], the colour populations
 // rebuilt from the state that collided (the colour source (phi, r n) of each
-// node, formed from its moments and normal).  Runs after the
-// refill, which has written the moments of the fresh nodes; clears their FRESH
-// mark.  Solid nodes get (rho0, solid_phi(mask)), so that stencils can tell solids
+// node, formed from its moments and normal).  The refill writes the moments of
+// the fresh nodes; this pass clears their FRESH mark.  Solid nodes get (rho0, solid_phi(mask)), so that stencils can tell solids
 // from phi alone.
 //
 // A block takes an x-y tile of the simulation's moments tiling and marches up
@@ -178,7 +296,6 @@ __device__ __forceinline__ void moments_block(const Batch& bt, const SimDev& s, 
   auto& kinds = lds.kinds;
   const int N = (int)s.N;
   const int nx = s.nx, ny = s.ny, nz = s.nz, P = nx * ny;
-  if (sb.y == 0 && threadIdx.x == 0) s.counters[0] = 0u;  // fresh list consumed
   const GLB float* __restrict__ NX = gp((const float*)s.nrm);
   const float hb = 0.5f * s.beta;
   const GLB T* __restrict__ pops = gp((const T*)s.pops[bt.cur]);
@@ -339,10 +456,23 @@ __device__ __forceinline__ void moments_block(const Batch& bt, const SimDev& s, 
 // W64: every simulation of the launch has 64-wide tiles; else the tile width
 // is the block's simulation's (an ensemble mixes them: one uniform branch per
 // block, against offsets computed from a width in a register, see k_interface)
+// The first nsim x nref blocks refill (the longest chains start first).
 template <int STORE, bool W64>
-__global__ __launch_bounds__(256) void k_moments(Batch bt) {
-  __shared__ MomLds lds;
-  const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
+// four waves per SIMD (128 VGPRs): the refill's loads alone would take 141
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_moments(
+    Batch bt, int nref) {
+  __shared__ union {
+    MomLds mom;
+    RefillLds ref;
+  } u;
+  const int first = bt.nsim * nref;
+  if ((int)blockIdx.x < first) {
+    const int si = (int)blockIdx.x / nref;
+    refill_block<STORE, REFILL_STEP>(bt, bt.tab[si], (int)blockIdx.x - si * nref, nref, u.ref);
+    return;
+  }
+  MomLds& lds = u.mom;
+  const int2 sb = batch_block_in(bt, bt.mblk, (int)blockIdx.x - first);
   const SimDev& s = bt.tab[sb.x];
   if (W64 || s.mtile_lx == 6)
     moments_block<STORE, 6>(bt, s, sb, lds);
@@ -359,7 +489,7 @@ __global__ __launch_bounds__(256) void k_moments_boundary(Batch bt) {
   const int2 sb = batch_block(bt, blockIdx.x);
   const SimDev& s = bt.tab[sb.x];
   int n, gx, gy, gz;
-  if (sb.y == 0 && threadIdx.x == 0) s.counters[0] = 0u;
+  if (sb.y == 0 && threadIdx.x == 0) s.counters[bt.fc] = 0u;  // fresh list consumed
   if (!tile_node(s, sb.y, n, gx, gy, gz)) return;
   const uint16_t m = s.mask[n];
   if (m & FRESH_BIT) {
@@ -1062,6 +1192,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   }
 }
 
+// per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
+// (G after the wetting rotation, from the step's normal field)
+__device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, int p) {
+  DevParticle& P = s.P[p];
+  const int B = s.cap_B;
+  int org[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) org[k] = (int)floor(P.x[k] - P.R);
+  if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
+  float4* box = s.capbox + (long long)p * B * B * B;
+  // the record's fields held in registers (the box stores may alias the record)
+  const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
+  const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd ^ 1]) + N;
+  const GLB float* __restrict__ NRM = gp((const float*)s.nrm);
+  const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
+  // a particle whose box holds no fluid node with |G| near EPS_G or above gets
+  // no force: every point's G is a convex combination of corner values, so it
+  // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
+  // rounding); the box's nodes say so here, once, for that kernel
+  bool iface = false;
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < B * B * B; k += gridDim.x * blockDim.x) {
+    const int ix = k % B, iy = (k / B) % B, iz = k / (B * B);
+    const int x = wrapi(org[0] + ix, nx), y = wrapi(org[1] + iy, ny), z = wrapi(org[2] + iz, nz);
+    const unsigned n = (unsigned)(x + nx * (y + ny * z));
+    // every plane read at once and the solid case taken by selects (a load
+    // used only inside a branch is made there, a second round trip)
+    const float gw = at(NRM + 3 * N, n), ph = at(PHI, n);
+    const float n0 = at(NRM, n), n1 = at(NRM + N, n), n2 = at(NRM + 2 * N, n);
+    const uint8_t kind = KIND[kind_index(s, x, y, z)];
+    // G = n max(|G|, EPS_G): the colour gradient after the wetting rotation;
+    // phi = 2 marks a solid node; on a pure tile plane G is zero and its
+    // normal planes are not looked at
+    const bool fl = !(ph > PHI_SOLID_TEST), mixed = fl && kind == KIND_MIXED;
+    const float gm = fmaxf(gw, EPS_G);
+    const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
+                                 mixed ? n2 * gm : 0.f);
+    box[k] = v;
+    iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
+  }
+  if (__syncthreads_or(iface) && threadIdx.x == 0) P.cap_on = 1;
+}
+
 // Moving-wall correction and momentum exchange on particle links, after
 // k_fused has bounced f*_i back into direction opp(i) at the fluid node x:
 // f_opp(x) += 6 w_i rho(x) (c_opp . u_w) (its colour share phi(x) is added by
@@ -1069,9 +1241,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 // u_w = V + Omega x (x + c_i/2 - X) (half-way bounce-back eqs.), and the
 // momentum given to the particle dP = (c_i - u_w) f*_i - (c_opp - u_w) f_opp
 // (hydrodynamic force eqs.), summed in FP64 per particle.  One grid row per
-// particle over the nodes of its bounding box grown by one.
+// particle over the nodes of its bounding box grown by one; with capillary
+// forces a second row per particle fills its capillary box, which needs nothing
+// of the first (both wait on memory: 66 + 21 -> 70 us with 500 spheres, 11 + 4
+// -> 11 us with one).
 template <int STORE>
-__global__ __launch_bounds__(256) void k_links(Batch bt) {
+__global__ __launch_bounds__(256) void k_links(Batch bt, int np_rows) {
+  if ((int)blockIdx.y >= np_rows) {
+    const int2 cp = batch_particle(bt, (int)blockIdx.y - np_rows);
+    capillary_box(bt, bt.tab[cp.x], cp.y);
+    return;
+  }
   // one thread per node of the particle's box; runs after k_fused, before the
   // buffers swap: src holds the state it read, dst the state it wrote
   using IO = Codec<STORE>;
@@ -1239,36 +1419,64 @@ hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int mode, fl
   return hipGetLastError();
 }
 
-hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, hipStream_t st) {
+// cap: fill the capillary boxes too
+hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, bool cap,
+                        hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
-  // the box of k_links spans at most 2 R + 6 nodes per axis, R <= (Bmask - 5) / 2
+  // the box of k_links spans at most 2 R + 6 nodes per axis, R <= (Bmask - 5) / 2,
+  // the capillary box fewer
   const long long B = Bmax + 1;
-  const dim3 grid((unsigned)((B * B * B + 255) / 256), np_rows);
+  const dim3 grid((unsigned)((B * B * B + 255) / 256), cap ? 2 * np_rows : np_rows);
   if (storage == 0)
-    hipLaunchKernelGGL(k_links<0>, grid, dim3(256), 0, st, b);
+    hipLaunchKernelGGL(k_links<0>, grid, dim3(256), 0, st, b, np_rows);
   else
-    hipLaunchKernelGGL(k_links<1>, grid, dim3(256), 0, st, b);
+    hipLaunchKernelGGL(k_links<1>, grid, dim3(256), 0, st, b, np_rows);
   return hipGetLastError();
 }
 
-// mode MOM_STEP (in a step, after the refill; mnblk blocks of the moments
-// tiling) or MOM_BOUNDARY (between steps; nblk per-node blocks)
-enum { MOM_STEP = 0, MOM_BOUNDARY = 1 };
-hipError_t launch_moments(const Batch& b, int storage, unsigned nblk, unsigned mnblk, int mode,
-                          hipStream_t st) {
-  if (mode == MOM_BOUNDARY)
-    hipLaunchKernelGGL(k_moments_boundary, dim3(nblk), dim3(256), 0, st, b);
-  else if (storage == 0) {
+// Blocks of 14 fresh nodes per simulation that refill: two per particle of the
+// busiest simulation (128 to 1,024 in all for one simulation; at least four for
+// each of a batch).  The fresh nodes of a step scale with the moving particles,
+// and a block that must take a second round of them doubles the dependent chain
+// (500 spheres: 196 -> 185 us for the particle phase with 1,000 blocks instead of
+// 128); a batch's idle blocks cost too (64 boxes with 128 each: 16 us).
+static int refill_blocks(size_t fresh_cap_max, int np_max, int nsim) {
+  if (fresh_cap_max == 0) return 0;
+  const size_t all = (fresh_cap_max + REFILL_PER - 1) / REFILL_PER;
+  const int least = nsim == 1 ? 128 : 4;
+  return (int)std::min<size_t>(all, (size_t)std::min(1024, std::max(least, 2 * np_max)));
+}
+
+// in a step: the refill of the fresh nodes and the moments of all others; mnblk
+// blocks of the moments tiling, fresh_cap_max: the largest fresh-list capacity of
+// the batch (0: no refill), np_max: the most particles of one simulation
+hipError_t launch_moments(const Batch& b, int storage, unsigned mnblk, size_t fresh_cap_max,
+                          int np_max, hipStream_t st) {
+  const int nref = refill_blocks(fresh_cap_max, np_max, b.nsim);
+  const dim3 g(mnblk + (unsigned)(b.nsim * nref)), t(256);
+  if (storage == 0) {
     if (b.mlx == 6)
-      hipLaunchKernelGGL((k_moments<0, true>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_moments<0, true>), g, t, 0, st, b, nref);
     else
-      hipLaunchKernelGGL((k_moments<0, false>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_moments<0, false>), g, t, 0, st, b, nref);
   } else {
     if (b.mlx == 6)
-      hipLaunchKernelGGL((k_moments<1, true>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_moments<1, true>), g, t, 0, st, b, nref);
     else
-      hipLaunchKernelGGL((k_moments<1, false>), dim3(mnblk), dim3(256), 0, st, b);
+      hipLaunchKernelGGL((k_moments<1, false>), g, t, 0, st, b, nref);
   }
+  return hipGetLastError();
+}
+
+// between steps, after the mask changed (one simulation; nblk per-node blocks)
+hipError_t launch_boundary(const Batch& b, int storage, unsigned nblk, size_t fresh_cap_max,
+                           int np_max, hipStream_t st) {
+  const int nref = refill_blocks(fresh_cap_max, np_max, b.nsim);
+  if (nref > 0 && storage == 0)
+    hipLaunchKernelGGL(k_refill_boundary<0>, dim3(nref, b.nsim), dim3(256), 0, st, b);
+  else if (nref > 0)
+    hipLaunchKernelGGL(k_refill_boundary<1>, dim3(nref, b.nsim), dim3(256), 0, st, b);
+  hipLaunchKernelGGL(k_moments_boundary, dim3(nblk), dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
 // lbm_particles.hip -- particle kernels of liblbm for gfx950: solid mask update,
-// refilling of fresh fluid nodes, capillary force on the Lagrangian surface grid
-// and the DEM (contacts with sliding and rolling friction, velocity Verlet).
+// capillary force on the Lagrangian surface grid and the DEM (contacts with sliding and rolling friction, velocity Verlet).
 #include <algorithm>
 
 #include "lbm_device.h"
@@ -124,7 +123,7 @@ __global__ __launch_bounds__(256) void k_mask(Batch bt) {
     if (want) {
       const int lane = (int)(threadIdx.x & 63), first = __ffsll((long long)want) - 1;
       uint32_t base0 = 0;
-      if (lane == first) base0 = atomicAdd(&s.counters[0], (uint32_t)__popcll(want));
+      if (lane == first) base0 = atomicAdd(&s.counters[bt.fc], (uint32_t)__popcll(want));
       base0 = (uint32_t)__shfl((int)base0, first, 64);
       if (fresh) {
         MASK[no] = FRESH_BIT;
@@ -142,153 +141,7 @@ __global__ __launch_bounds__(256) void k_mask(Batch bt) {
   if (in && m == 0 && owner(x, y, z) == p) MASK[n] = (uint16_t)(2 + p);
 }
 
-// Refilling (refilling eqs.): f_a, f_b of a fresh node = equilibria of the mean
-// neighbour densities (fluid, not fresh, D3Q19 neighbours; rho0/2 each if none)
-// at the surface velocity of the particle that uncovered it.  Stored are the
-// total f and the node's moments (rho, phi) in rp[rd ^ 1].  The neighbour
-// densities are those of the post-stream state: in a step (REFILL_STEP) rebuilt
-// from the state that collided, as the moments pass does; between steps
-// (REFILL_BOUNDARY) the current moments rp[rd ^ 1].
-enum { REFILL_STEP = 0, REFILL_BOUNDARY = 1 };
-template <int STORE, int MODE>
-__global__ __launch_bounds__(256) void k_refill(Batch bt) {
-  // one thread per (fresh node, neighbour direction): 14 fresh nodes per
-  // block; grid row = simulation
-  using IO = Codec<STORE>;
-  using T = typename IO::T;
-  const SimDev& s = bt.tab[blockIdx.y];
-  if (s.np == 0) return;
-  T* b = (T*)s.pops[bt.cur];
-  const GLB float* RO = gp((const float*)s.rp[bt.rd]);
-  float* RN = s.rp[bt.rd ^ 1];
-  constexpr int PER = 14;
-  __shared__ float sh_a[PER][18], sh_b[PER][18];
-  __shared__ int sh_c[PER][18];
-  const uint32_t cnt = min(s.counters[0], s.fresh_cap);
-  const int N = (int)s.N;
-  const int slot = threadIdx.x / 18, dir = threadIdx.x % 18 + 1;
-  for (uint32_t base = blockIdx.x * PER; base < cnt; base += gridDim.x * PER) {
-    const uint32_t k = base + slot;
-    if (slot < PER) {
-      float ra = 0.f, rb = 0.f;
-      int c = 0;
-      if (k < cnt) {
-        const int n = (int)s.fresh[k];
-        const int x = n % s.nx, y = (n / s.nx) % s.ny, z = n / (s.nx * s.ny);
-        const int mx = wrapi(x + cx(dir), s.nx), my = wrapi(y + cy(dir), s.ny),
-                  mz = wrapi(z + cz(dir), s.nz);
-        const int m = mx + s.nx * (my + s.ny * mz);
-        if (s.mask[m] == 0) {
-          float rho, sg;
-          if (MODE == REFILL_STEP) {
-            const Nbr nbm(mx, my, mz, s.nx, s.ny, s.nz);
-            rebuild_moments<STORE>(gp((const T*)b), RO, gp((const float*)s.nrm), N, m, nbm,
-                                   s.rho0, 0.5f * s.beta, STORE ? RO[m] : 0.f, rho, sg);
-          } else {
-            // FP32 keeps no density where phi is +-1
-            const float ph = RN[N + m];
-            rho = STORE == 0 && phi_pure(ph)
-                      ? node_density<STORE>(gp((const T*)b), N, m, s.rho0, 0.f)
-                      : RN[m];
-            sg = rho * ph;
-          }
-          ra = 0.5f * (rho + sg);
-          rb = 0.5f * (rho - sg);
-          c = 1;
-        }
-      }
-      sh_a[slot][dir - 1] = ra;
-      sh_b[slot][dir - 1] = rb;
-      sh_c[slot][dir - 1] = c;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < PER && base + threadIdx.x < cnt) {
-      const uint32_t kk = base + threadIdx.x;
-      float sa = 0.f, sb = 0.f;
-      int c = 0;
-      for (int i = 0; i < 18; ++i) {
-        sa += sh_a[threadIdx.x][i];
-        sb += sh_b[threadIdx.x][i];
-        c += sh_c[threadIdx.x][i];
-      }
-      const int n = (int)s.fresh[kk];
-      const int p = (int)s.fresh_own[kk];
-      const int x = n % s.nx, y = (n / s.nx) % s.ny, z = n / (s.nx * s.ny);
-      const float ra = c ? sa / c : 0.5f * s.rho0;
-      const float rb = c ? sb / c : 0.5f * s.rho0;
-      const DevParticle& P = s.P[p];
-      const double rx = wrapd((double)x - P.x[0], (double)s.nx);
-      const double ry = wrapd((double)y - P.x[1], (double)s.ny);
-      const double rz = wrapd((double)z - P.x[2], (double)s.nz);
-      const float ux = (float)(P.v[0] + P.w[1] * rz - P.w[2] * ry);
-      const float uy = (float)(P.v[1] + P.w[2] * rx - P.w[0] * rz);
-      const float uz = (float)(P.v[2] + P.w[0] * ry - P.w[1] * rx);
-      const float uu = ux * ux + uy * uy + uz * uz;
-      const float rho = ra + rb;
-      // FP16: encoded with the reference the decoders of this state use
-      const float Rn = STORE ? RO[n] : 0.f;
-      for (int q = 0; q < Q; ++q) {
-        const float cu = cx(q) * ux + cy(q) * uy + cz(q) * uz;
-        const float poly = 3.0f * cu + 4.5f * cu * cu - 1.5f * uu;
-        const float dq = wq(q) * ((rho - s.rho0) + rho * poly);
-        IO::st(b + pidx(q, N, n), wq(q) * s.rho0, 1.0f / (wq(q) * s.rho0), wq(q) * Rn, dq);
-      }
-      // f^a - f^b = (ra - rb) / rho f: the order parameter of the node
-      RN[n] = rho;
-      RN[N + n] = (ra - rb) / rho;
-    }
-    __syncthreads();
-  }
-}
-
 // -------------------------------------------------------------- capillary
-// per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
-// (G after the wetting rotation, from the step's normal field)
-__global__ void k_capbox(Batch bt) {
-  const int2 sp = batch_particle(bt, blockIdx.y);
-  const SimDev& s = bt.tab[sp.x];
-  const int p = sp.y;
-  DevParticle& P = s.P[p];
-  const int B = s.cap_B;
-  int org[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) org[k] = (int)floor(P.x[k] - P.R);
-  if (blockIdx.x == 0 && threadIdx.x < 3) s.capbox_org[3 * p + threadIdx.x] = org[threadIdx.x];
-  if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
-  float4* box = s.capbox + (long long)p * B * B * B;
-  // phi of the state that collided this step (the buffers have swapped); the
-  // record's fields held in registers (the box stores may alias the record)
-  const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
-  const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd]) + N;
-  const GLB float* __restrict__ NRM = gp((const float*)s.nrm);
-  const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
-  // a particle whose box holds no fluid node with |G| near EPS_G or above gets
-  // no force: every point's G is a convex combination of corner values, so it
-  // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
-  // rounding); the box's nodes say so here, once, for that kernel
-  bool iface = false;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < B * B * B; k += gridDim.x * blockDim.x) {
-    const int ix = k % B, iy = (k / B) % B, iz = k / (B * B);
-    const int x = wrapi(org[0] + ix, nx), y = wrapi(org[1] + iy, ny), z = wrapi(org[2] + iz, nz);
-    const unsigned n = (unsigned)(x + nx * (y + ny * z));
-    // every plane read at once and the solid case taken by selects (a load
-    // used only inside a branch is made there, a second round trip)
-    const float gw = at(NRM + 3 * N, n), ph = at(PHI, n);
-    const float n0 = at(NRM, n), n1 = at(NRM + N, n), n2 = at(NRM + 2 * N, n);
-    const uint8_t kind = KIND[kind_index(s, x, y, z)];
-    // G = n max(|G|, EPS_G): the colour gradient after the wetting rotation;
-    // phi = 2 marks a solid node; on a pure tile plane G is zero and its
-    // normal planes are not looked at
-    const bool fl = !(ph > PHI_SOLID_TEST), mixed = fl && kind == KIND_MIXED;
-    const float gm = fmaxf(gw, EPS_G);
-    const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
-                                 mixed ? n2 * gm : 0.f);
-    box[k] = v;
-    iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
-  }
-  if (__syncthreads_or(iface) && threadIdx.x == 0) P.cap_on = 1;
-}
-
 // Capillary force (capillary-force eq.): sum over the polar/azimuthal grid of
 // sigma 9/2 k beta max(0, 1 - phi^2) dA sin(theta_p) m^, m^ = normalise(n_s - (n.n_s) n),
 // torque arm R n_s; phi and G trilinear over fluid corners.  A grid row of
@@ -702,7 +555,10 @@ __global__ __launch_bounds__(64) void k_dem_setup(Batch bt, int np_rows, int mas
   P.cap_on = 0;
   // the step counter advances here (the sub-steps' history record takes the
   // value before it)
-  if (i == 0) *s.step_counter += 1;
+  if (i == 0) {
+    *s.step_counter += 1;
+    s.counters[0] = 0u;  // the fresh list, which the mask update fills again
+  }
   int* nb = s.nb + (long long)i * MAXNB;
   int c = 0;
   // membership of a partner in this step's candidate list, from registers (a
@@ -1249,7 +1105,10 @@ __global__ __launch_bounds__(DEM_SMALL * DEM_LANES) void k_dem(Batch bt) {
       h[21 + c] = V;
     }
   }
-  if (threadIdx.x == 0) *s.step_counter = step + 1;
+  if (threadIdx.x == 0) {
+    *s.step_counter = step + 1;
+    s.counters[0] = 0u;  // the fresh list, which the mask update fills again
+  }
 }
 
 // ------------------------------------------------------------ host launchers
@@ -1269,39 +1128,9 @@ hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_r
   return hipGetLastError();
 }
 
-// fresh_cap_max: the largest fresh-list capacity of the batch; np_max: the
-// most particles of one simulation; mode REFILL_STEP (in a step) or
-// REFILL_BOUNDARY (between steps).  The grid row takes two blocks of 14 fresh
-// nodes per particle (128 to 1,024): the fresh nodes of a step scale with the
-// moving particles, and a block that must take a second round of them doubles
-// the kernel's dependent chain (500 spheres: 196 -> 185 us for the particle
-// phase with 1,000 blocks instead of 128)
-hipError_t launch_refill(const Batch& b, int storage, size_t fresh_cap_max, int np_max, int mode,
-                         hipStream_t st) {
-  if (fresh_cap_max == 0) return hipSuccess;
-  unsigned nb = (unsigned)((fresh_cap_max + 13) / 14);
-  const unsigned cap = (unsigned)std::min(1024, std::max(128, 2 * np_max));
-  if (nb > cap) nb = cap;
-  if (nb == 0) nb = 1;
-  const dim3 grid(nb, b.nsim);
-  if (storage == 0) {
-    if (mode == REFILL_STEP)
-      hipLaunchKernelGGL((k_refill<0, REFILL_STEP>), grid, dim3(256), 0, st, b);
-    else
-      hipLaunchKernelGGL((k_refill<0, REFILL_BOUNDARY>), grid, dim3(256), 0, st, b);
-  } else {
-    if (mode == REFILL_STEP)
-      hipLaunchKernelGGL((k_refill<1, REFILL_STEP>), grid, dim3(256), 0, st, b);
-    else
-      hipLaunchKernelGGL((k_refill<1, REFILL_BOUNDARY>), grid, dim3(256), 0, st, b);
-  }
-  return hipGetLastError();
-}
-
-// cap_B: the largest capillary-box side; npts: Lagrangian points per particle
-hipError_t launch_capillary(const Batch& b, int np_rows, int cap_B, int npts, hipStream_t st) {
+// npts: Lagrangian points per particle
+hipError_t launch_capillary(const Batch& b, int np_rows, int npts, hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_capbox, dim3(box_blocks(cap_B), np_rows), dim3(256), 0, st, b);
   // workgroups per particle: four points per thread, or down to one where
   // few particles leave the GPU idle (about 2,048 workgroups in all)
   const int wide = std::min(npts / 256, (2048 + np_rows - 1) / np_rows);
