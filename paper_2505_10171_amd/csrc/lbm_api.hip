@@ -41,6 +41,7 @@ hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, doubl
 hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
 hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
                               hipStream_t st);
+hipError_t launch_push(const SimDev& s, hipStream_t st);
 hipError_t launch_capillary(const Batch& b, int np_rows, int npts, hipStream_t st);
 hipError_t launch_dem(const Batch& b, int np_max, int np_rows, int n_sub_max, hipStream_t st);
 }  // namespace lbm
@@ -87,7 +88,7 @@ struct SimLayout {
   int np, Bmask, Bcap, hist_cap;
   size_t pop_bytes, fresh_cap;
   size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_fresh, off_fresh_own,
-      off_counters, off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_mass,
+      off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_mass,
       off_step;
   size_t total;
 };
@@ -202,7 +203,6 @@ SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
   (void)take(4 * L.N);  // unused: callers rely on 46 bytes per node besides the populations
   L.off_fresh = take(4 * L.fresh_cap);
   L.off_fresh_own = take(4 * L.fresh_cap);
-  L.off_counters = take(64);
   L.off_P = take(sizeof(DevParticle) * L.np);
   L.off_ct = take(sizeof(Contact) * (size_t)L.np * MAXC);
   L.off_nb = take(sizeof(int) * (size_t)L.np * MAXNB);
@@ -316,6 +316,7 @@ struct lbm_ctx {
   SimDev* d_tab = nullptr;
   uint32_t* d_blk = nullptr;
   uint32_t* d_mblk = nullptr;
+  uint32_t* d_counters = nullptr;  // COUNTERS words per simulation, one after another
   int2* d_pmap = nullptr;
   unsigned nblk = 0;
   int np_rows = 0, np_max = 0, Bmax = 0, npts = 0, n_sub_max = 1;
@@ -457,10 +458,14 @@ static Batch batch_one(const lbm_ctx* c, int si) {
                c->sims[si].d.mtile_lx, c->sims[si].solo, 0};
 }
 
-// workspace tail holding the batch tables
+// device words of a simulation's counters (SimDev::counters)
+constexpr int COUNTERS = 16;
+
+// workspace tail holding the batch tables and the counters
 static size_t batch_tables_bytes(int n_sims, long long np_total) {
   return align_up(sizeof(SimDev) * (size_t)n_sims) + 2 * align_up(4 * (size_t)(n_sims + 1)) +
-         align_up(8 * (size_t)std::max<long long>(np_total, 1));
+         align_up(8 * (size_t)std::max<long long>(np_total, 1)) +
+         align_up(4 * (size_t)COUNTERS * n_sims);
 }
 
 static int set_err(lbm_ctx* c, int code, const char* fmt, ...) {
@@ -496,6 +501,13 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
     ctx->d_mblk = (uint32_t*)b;
     b += align_up(4 * (size_t)(n_sims + 1));
     ctx->d_pmap = (int2*)b;
+    size_t np_total = 0;
+    for (const SimHost& sh : ctx->sims) np_total += (size_t)sh.d.np;
+    b += align_up(8 * std::max<size_t>(np_total, 1));
+    ctx->d_counters = (uint32_t*)b;
+    for (int si = 0; si < n_sims; ++si)
+      ctx->sims[si].d.counters = ctx->d_counters + (size_t)COUNTERS * si;
+    HIPCHK(ctx, hipMemsetAsync(ctx->d_counters, 0, 4 * (size_t)COUNTERS * n_sims, ctx->stream));
   }
   std::vector<SimDev> tab(n_sims);
   std::vector<uint32_t> blk(n_sims + 1, 0), mblk(n_sims + 1, 0);
@@ -662,7 +674,6 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     d.mask = (uint16_t*)(b + sh.L.off_mask);
     d.fresh = (uint32_t*)(b + sh.L.off_fresh);
     d.fresh_own = (uint32_t*)(b + sh.L.off_fresh_own);
-    d.counters = (uint32_t*)(b + sh.L.off_counters);
     d.fresh_cap = (uint32_t)sh.L.fresh_cap;
     d.P = (DevParticle*)(b + sh.L.off_P);
     d.ct = (Contact*)(b + sh.L.off_ct);
@@ -709,8 +720,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
           hipStreamSynchronize(st) != hipSuccess)
         return fail(LBM_EHIP, "particle upload failed");
     }
-    if (hipMemsetAsync(d.counters, 0, 64, st) != hipSuccess ||
-        hipMemsetAsync(d.step_counter, 0, sizeof(unsigned long long), st) != hipSuccess)
+    if (hipMemsetAsync(d.step_counter, 0, sizeof(unsigned long long), st) != hipSuccess)
       return fail(LBM_EHIP, "counter initialisation failed");
     // phi0 staged in the phi plane of rp[0]
     if (phi0 && phi0[si]) {
@@ -1039,14 +1049,17 @@ int lbm_profile_read(lbm_ctx* ctx, double* total_ms, int64_t* launches, int32_t 
   return LBM_OK;
 }
 
-// device status words of every simulation (only = one simulation's)
+// Device status words of every simulation (only = one simulation's), in one
+// copy (an ensemble of 64 read by itself, one simulation at a time, had spent
+// 64 copies and waits on each); waits for the stream
 static int check_status(lbm_ctx* ctx, int only = -1) {
-  for (int si = 0; si < (int)ctx->sims.size(); ++si) {
-    if (only >= 0 && si != only) continue;
-    const SimHost& sh = ctx->sims[si];
-    uint32_t cnt[4];
-    HIPCHK(ctx, hipMemcpyAsync(cnt, sh.d.counters, sizeof cnt, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  const int first = only >= 0 ? only : 0, n = only >= 0 ? 1 : (int)ctx->sims.size();
+  std::vector<uint32_t> words((size_t)COUNTERS * n);
+  HIPCHK(ctx, hipMemcpyAsync(words.data(), ctx->d_counters + (size_t)COUNTERS * first,
+                             4 * words.size(), hipMemcpyDeviceToHost, ctx->stream));
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  for (int k = 0; k < n; ++k) {
+    const uint32_t* cnt = &words[(size_t)COUNTERS * k];
     if (cnt[1] & ST_UNSTABLE)
       return set_err(ctx, LBM_EUNSTABLE, "unstable flow: NaN, rho <= 0 or |u| > 0.3");
     if (cnt[1] & ST_CONTACT_FULL)
@@ -1061,7 +1074,6 @@ static int check_status(lbm_ctx* ctx, int only = -1) {
 int lbm_sync(lbm_ctx* ctx) {
   if (!ctx) return LBM_EINVAL;
   if (ctx->err) return LBM_ESTATE;
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   return check_status(ctx);
 }
 
@@ -1078,16 +1090,16 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
   if (!sh) return set_err(ctx, LBM_ERANGE, "simulation index out of range");
   SimDev& d = sh->d;
   if (n != d.np || (n > 0 && !parts)) return set_err(ctx, LBM_EINVAL, "particle count mismatch");
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  int rc = check_status(ctx, sim);
+  // (a push reports the status when it is done)
+  int rc = dir == 0 ? check_status(ctx, sim) : LBM_OK;
   if (rc) return rc;
   if (n_hist) *n_hist = 0;
-  if (d.np == 0) return LBM_OK;
-  std::vector<DevParticle> hp(d.np);
-  HIPCHK(ctx, hipMemcpyAsync(hp.data(), d.P, sizeof(DevParticle) * d.np, hipMemcpyDeviceToHost,
-                             ctx->stream));
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  if (d.np == 0) return check_status(ctx, sim);
   if (dir == 0) {
+    std::vector<DevParticle> hp(d.np);
+    HIPCHK(ctx, hipMemcpyAsync(hp.data(), d.P, sizeof(DevParticle) * d.np, hipMemcpyDeviceToHost,
+                               ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     for (int p = 0; p < d.np; ++p) {
       const DevParticle& s = hp[p];
       lbm_particle& o = parts[p];
@@ -1139,15 +1151,18 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
     if (parts[p].R > sh->Rmax)
       return set_err(ctx, LBM_ERANGE, "radius exceeds the largest radius the context was sized for");
   }
+  // the state and properties lead the record; they are staged where the DEM keeps
+  // its views, which no step reads before it writes them
+  std::vector<DevParticleHead> head(d.np);
   for (int p = 0; p < d.np; ++p) {
-    DevParticle& s = hp[p];
-    for (int k = 0; k < 3; ++k) s.xo[k] = s.x[k];
-    s.Ro = s.R;
+    DevParticle s;
+    memset(&s, 0, sizeof s);
     fill_dev_particle(s, parts[p], sh->cfg.delta_R, true);
+    memcpy(&head[p], &s, sizeof(DevParticleHead));
   }
-  HIPCHK(ctx, hipMemcpyAsync(d.P, hp.data(), sizeof(DevParticle) * d.np, hipMemcpyHostToDevice,
-                             ctx->stream));
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  HIPCHK(ctx, hipMemcpyAsync(d.view, head.data(), sizeof(DevParticleHead) * d.np,
+                             hipMemcpyHostToDevice, ctx->stream));
+  HIPCHK(ctx, launch_push(d, ctx->stream));
   rc = post_dem_pipeline(ctx, sim, true);
   if (rc) return rc;
   return lbm_sync(ctx);
@@ -1168,22 +1183,26 @@ int lbm_fields2(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, 
   const long long N = d.N;
   const hipMemcpyKind kind = dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   if (what & (LBM_F_RHO | LBM_F_U | LBM_F_PHI | LBM_F_FORCE)) {
-    // the spare population buffer holds the outputs: rho | phi | u | F (8N floats)
+    // written straight to device buffers; for host buffers through the spare
+    // population buffer: rho | phi | u | F (8N floats)
     float* scratch = (float*)d.pops[ctx->cur ^ 1];
-    float* orho = scratch;
-    float* ophi = scratch + N;
-    float* ou = scratch + 2 * N;
-    float* oF = scratch + 5 * N;
+    auto out = [&](uint32_t bit, float* dst, long long off) -> float* {
+      if (!(what & bit) || !dst) return nullptr;
+      return dst_is_device ? dst : scratch + off;
+    };
+    float* orho = out(LBM_F_RHO, rho, 0);
+    float* ophi = out(LBM_F_PHI, phi, N);
+    float* ou = out(LBM_F_U, u, 2 * N);
+    float* oF = out(LBM_F_FORCE, force, 5 * N);
     const Batch b1 = batch_one(ctx, sim);
     HIPCHK(ctx, launch_interface(b1, mom_blocks(d, b1.mkz), ctx->stream));
     HIPCHK(ctx, launch_fused(b1, ctx->storage, sim_blocks(d), 1, orho, ou, ophi, oF, ctx->stream));
-    if ((what & LBM_F_FORCE) && force)
-      HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));
-    if ((what & LBM_F_RHO) && rho)
-      HIPCHK(ctx, hipMemcpyAsync(rho, orho, 4 * N, kind, ctx->stream));
-    if ((what & LBM_F_PHI) && phi)
-      HIPCHK(ctx, hipMemcpyAsync(phi, ophi, 4 * N, kind, ctx->stream));
-    if ((what & LBM_F_U) && u) HIPCHK(ctx, hipMemcpyAsync(u, ou, 12 * N, kind, ctx->stream));
+    if (!dst_is_device) {
+      if (oF) HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));
+      if (orho) HIPCHK(ctx, hipMemcpyAsync(rho, orho, 4 * N, kind, ctx->stream));
+      if (ophi) HIPCHK(ctx, hipMemcpyAsync(phi, ophi, 4 * N, kind, ctx->stream));
+      if (ou) HIPCHK(ctx, hipMemcpyAsync(u, ou, 12 * N, kind, ctx->stream));
+    }
   }
   if ((what & LBM_F_MASK) && mask)
     HIPCHK(ctx, hipMemcpyAsync(mask, d.mask, 2 * N, kind, ctx->stream));

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace lbm {
@@ -81,6 +82,12 @@ struct alignas(16) DevParticle {
   // or above (set by the box kernel, cleared by the DEM with the accumulators)
   int cap_on;
 };
+
+// the leading part of the record that a push replaces: x .. pad
+struct DevParticleHead {
+  double w[24];
+};
+static_assert(offsetof(DevParticle, Fh) == sizeof(DevParticleHead), "record head");
 
 constexpr int LBM_HIST_DOUBLES_DEV = 27;
 

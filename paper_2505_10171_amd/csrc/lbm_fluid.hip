@@ -1044,6 +1044,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
       STORE ? KIND_MIXED : gp((const uint8_t*)s.kind)[kind_index(s, gx, gy, gz)];
   uint32_t bits = 0u;
   if (kind >= KIND_PURE_A_SOLID) bits = __float_as_uint(at(cur, 2u * (unsigned)n + 1u));
+  // MODE_FIELDS: the fields that are asked for
+  auto put = [&](float r, float ph, float ux, float uy, float uz, float fx, float fy, float fz) {
+    if (out_rho) out_rho[n] = r;
+    if (out_phi) out_phi[n] = ph;
+    if (out_u) {
+      out_u[n] = ux;
+      out_u[N + n] = uy;
+      out_u[2 * N + n] = uz;
+    }
+    if (out_F) {
+      out_F[n] = fx;
+      out_F[N + n] = fy;
+      out_F[2 * N + n] = fz;
+    }
+  };
   auto solid_node = [&]() {
     if (MODE == MODE_FIELDS) {
       const uint16_t m0 = s.mask[n];
@@ -1057,14 +1072,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
         uy = (float)(P.v[1] + P.w[2] * rx - P.w[0] * rz);
         uz = (float)(P.v[2] + P.w[0] * ry - P.w[1] * rx);
       }
-      out_rho[n] = 0.f;
-      out_phi[n] = 0.f;
-      out_u[n] = ux;
-      out_u[N + n] = uy;
-      out_u[2 * N + n] = uz;
-      out_F[n] = 0.f;
-      out_F[N + n] = 0.f;
-      out_F[2 * N + n] = 0.f;
+      put(0.f, 0.f, ux, uy, uz, 0.f, 0.f, 0.f);
     }
   };
   if (bits & 0x80000000u) {
@@ -1119,14 +1127,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   const float uu = ux * ux + uy * uy + uz * uz;
 
   if (MODE == MODE_FIELDS) {
-    out_rho[n] = rho;
-    out_phi[n] = phi;
-    out_u[n] = ux;
-    out_u[N + n] = uy;
-    out_u[2 * N + n] = uz;
-    out_F[n] = Fx;
-    out_F[N + n] = Fy;
-    out_F[2 * N + n] = Fz;
+    put(rho, phi, ux, uy, uz, Fx, Fy, Fz);
     return;
   }
   if (!(rho > 0.f) || !(uu <= 0.09f)) atomicOr(&s.counters[1], (uint32_t)ST_UNSTABLE);

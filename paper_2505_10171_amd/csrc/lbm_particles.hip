@@ -41,6 +41,19 @@ __device__ __attribute__((noinline)) bool inside_sphere(int x, int y, int z, con
   return d2 < R * R;
 }
 
+// Pushed particles: the heads of their records, staged in the view buffer,
+// into the records, whose present centre and radius the mask update releases.
+static_assert(2 * sizeof(DemView) >= sizeof(DevParticleHead), "the views hold the heads");
+__global__ void k_push(SimDev s) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= s.np) return;
+  DevParticle& P = s.P[p];
+  const DevParticleHead h = ((const DevParticleHead*)s.view)[p];
+  for (int d = 0; d < 3; ++d) P.xo[d] = P.x[d];
+  P.Ro = P.R;
+  *(DevParticleHead*)&P = h;
+}
+
 // Mask of the new positions, one grid row of blocks per particle p.  A node's new
 // owner is the lowest particle inside which it lies.  With RELEASE, the nodes
 // that belonged to p (old box) pass to their new owner or become fluid (fresh);
@@ -1115,6 +1128,11 @@ __global__ __launch_bounds__(DEM_SMALL * DEM_LANES) void k_dem(Batch bt) {
 static inline unsigned box_blocks(int B) {
   const int v = B * B * B;
   return (unsigned)((v + 255) / 256);
+}
+
+hipError_t launch_push(const SimDev& s, hipStream_t st) {
+  hipLaunchKernelGGL(k_push, dim3((unsigned)((s.np + 63) / 64)), dim3(64), 0, st, s);
+  return hipGetLastError();
 }
 
 hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,

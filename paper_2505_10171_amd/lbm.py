@@ -145,13 +145,18 @@ def make_particles(parts):
     return arr
 
 
-def particle_dict(o: LbmParticle) -> dict:
-    d = {k: np.array(getattr(o, k)[:]) for k in ("x", "v", "w", "q", "F_hyd", "T_hyd", "F_cap",
-                                                  "T_cap", "F_con", "T_con")}
-    for k in ("R", "rho_p", "theta_deg", "mu_s", "mu_r", "g_p"):
-        d[k] = getattr(o, k)
-    d["kinematic"] = o.kinematic
-    return d
+_VECTORS = ("x", "v", "w", "q", "F_hyd", "T_hyd", "F_cap", "T_cap", "F_con", "T_con")
+_SCALARS = ("R", "rho_p", "theta_deg", "mu_s", "mu_r", "g_p", "kinematic")
+_PARTICLE_DTYPE = np.dtype(LbmParticle)
+
+
+def particle_dicts(arr, n: int) -> list:
+    """The first n records as dictionaries: vectors as arrays (rows of one copy
+    per quantity), the rest as Python numbers."""
+    a = np.frombuffer(arr, dtype=_PARTICLE_DTYPE, count=n)
+    cols = [list(np.array(a[k])) for k in _VECTORS] + [a[k].tolist() for k in _SCALARS]
+    keys = _VECTORS + _SCALARS
+    return [dict(zip(keys, row)) for row in zip(*cols)]
 
 
 class Context:
@@ -240,7 +245,7 @@ class Context:
         self._check(load_library().lbm_particles_sync(self.h, sim, 0, arr, n, hptr,
                                                       self.history_steps if hptr else 0,
                                                       C.byref(nh)))
-        parts = [particle_dict(arr[i]) for i in range(n)]
+        parts = particle_dicts(arr, n)
         if history:
             h = (hbuf[: nh.value * n * HIST_DOUBLES].reshape(nh.value, n, HIST_DOUBLES)
                  if hbuf is not None else np.zeros((0, n, HIST_DOUBLES)))
