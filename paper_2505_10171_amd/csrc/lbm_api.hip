@@ -3,8 +3,8 @@
 // The context carves the caller's device workspace, uploads the initial state,
 // and issues the per-step kernel sequence on the caller's stream:
 //   k_fused (collide + recolour + stream + bounce-back + momentum exchange)
-//   k_links (moving walls, momentum exchange, capillary boxes) and k_capillary
-//   (capillary force)                            -- if the sim has particles
+//   k_links (moving walls, momentum exchange, capillary force; its capillary
+//   boxes are filled with k_fused)               -- if the sim has particles
 //   k_dem (contacts, friction, Verlet sub-steps)
 //   k_mask (solid mask of the new positions)
 //   k_moments (fresh fluid nodes refilled, order parameter of the new state)
@@ -26,9 +26,11 @@
 
 namespace lbm {
 hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st);
-hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int mode, float* orho,
-                        float* ou, float* ophi, float* oF, hipStream_t st);
-hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, bool cap,
+hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows, int Bcap,
+                        hipStream_t st);
+hipError_t launch_fields(const Batch& b, int storage, unsigned nblk, float* orho, float* ou,
+                         float* ophi, float* oF, hipStream_t st);
+hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, int npts,
                         hipStream_t st);
 hipError_t launch_moments(const Batch& b, int storage, unsigned mnblk, size_t fresh_cap_max,
                           int np_max, hipStream_t st);
@@ -42,7 +44,6 @@ hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
 hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
                               hipStream_t st);
 hipError_t launch_push(const SimDev& s, hipStream_t st);
-hipError_t launch_capillary(const Batch& b, int np_rows, int npts, hipStream_t st);
 hipError_t launch_dem(const Batch& b, int np_max, int np_rows, int n_sub_max, hipStream_t st);
 }  // namespace lbm
 
@@ -319,7 +320,7 @@ struct lbm_ctx {
   uint32_t* d_counters = nullptr;  // COUNTERS words per simulation, one after another
   int2* d_pmap = nullptr;
   unsigned nblk = 0;
-  int np_rows = 0, np_max = 0, Bmax = 0, npts = 0, n_sub_max = 1;
+  int np_rows = 0, np_max = 0, Bmax = 0, Bcap_max = 0, npts = 0, n_sub_max = 1;
   bool cap_needed = false;  // some simulation with particles has a capillary force
   size_t fresh_cap_max = 0;
   unsigned mnblk = 0;  // blocks of the moments pass over the batch
@@ -512,7 +513,7 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
   std::vector<SimDev> tab(n_sims);
   std::vector<uint32_t> blk(n_sims + 1, 0), mblk(n_sims + 1, 0);
   std::vector<int2> pmap;
-  ctx->np_max = ctx->Bmax = ctx->npts = 0;
+  ctx->np_max = ctx->Bmax = ctx->Bcap_max = ctx->npts = 0;
   ctx->cap_needed = false;
   ctx->n_sub_max = 1;
   ctx->fresh_cap_max = 0;
@@ -530,6 +531,7 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
     if (sh.d.np > 0) ctx->n_sub_max = std::max(ctx->n_sub_max, sh.d.n_sub);
     if (sh.d.np > 0) {
       ctx->Bmax = std::max(ctx->Bmax, sh.L.Bmask);
+      ctx->Bcap_max = std::max(ctx->Bcap_max, sh.L.Bcap);
       ctx->npts = std::max(ctx->npts, sh.d.cap_na * sh.d.cap_nphi);
       ctx->cap_needed |= sh.d.cap_pref != 0.0;
       ctx->fresh_cap_max = std::max(ctx->fresh_cap_max, (size_t)sh.d.fresh_cap);
@@ -786,17 +788,18 @@ static int step_once(lbm_ctx* ctx, int slot) {
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][0], st));
   HIPCHK(ctx, launch_interface(b, ctx->mnblk, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][1], st));
-  HIPCHK(ctx, launch_fused(b, ctx->storage, ctx->nblk, 0, nullptr, nullptr, nullptr, nullptr, st));
+  // without surface tension (sigma = 0) the capillary force is zero: the DEM
+  // reads the accumulators it cleared itself
+  HIPCHK(ctx, launch_fused(b, ctx->storage, ctx->nblk, ctx->cap_needed ? ctx->np_rows : 0,
+                           ctx->Bcap_max, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][2], st));
-  HIPCHK(ctx, launch_links(b, ctx->storage, ctx->np_rows, ctx->Bmax, ctx->cap_needed, st));
+  HIPCHK(ctx, launch_links(b, ctx->storage, ctx->np_rows, ctx->Bmax,
+                           ctx->cap_needed ? ctx->npts : 0, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][3], st));
   ctx->cur ^= 1;
   ctx->rd ^= 1;
   const Batch a = batch_all(ctx);
   if (ctx->np_rows > 0) {
-    // without surface tension (sigma = 0) the capillary force is zero: the DEM
-    // reads the accumulators it cleared itself
-    if (ctx->cap_needed) HIPCHK(ctx, launch_capillary(a, ctx->np_rows, ctx->npts, st));
     HIPCHK(ctx, launch_dem(a, ctx->np_max, ctx->np_rows, ctx->n_sub_max, st));
     HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->Bmax, true, st));
   }
@@ -944,7 +947,7 @@ int lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t* chosen) {
         for (int r = 0; r <= reps; ++r) {  // the first pass warms up
           if (r == 1) HIPCHK(ctx, hipEventRecord(e0, st));
           HIPCHK(ctx, launch_interface(b1, mom_blocks(d), st));
-          HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, nullptr, nullptr, nullptr, nullptr, st));
+          HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, 0, st));
           HIPCHK(ctx, launch_moments(a1, ctx->storage, mom_blocks(d), 0, 0, st));
         }
         HIPCHK(ctx, hipEventRecord(e1, st));
@@ -1196,7 +1199,7 @@ int lbm_fields2(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, 
     float* oF = out(LBM_F_FORCE, force, 5 * N);
     const Batch b1 = batch_one(ctx, sim);
     HIPCHK(ctx, launch_interface(b1, mom_blocks(d, b1.mkz), ctx->stream));
-    HIPCHK(ctx, launch_fused(b1, ctx->storage, sim_blocks(d), 1, orho, ou, ophi, oF, ctx->stream));
+    HIPCHK(ctx, launch_fields(b1, ctx->storage, sim_blocks(d), orho, ou, ophi, oF, ctx->stream));
     if (!dst_is_device) {
       if (oF) HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));
       if (orho) HIPCHK(ctx, hipMemcpyAsync(rho, orho, 4 * N, kind, ctx->stream));

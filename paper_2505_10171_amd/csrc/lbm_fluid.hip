@@ -1000,6 +1000,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
     interface_block<OPEN, 4>(bt, s, sb, lds);
 }
 
+// per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
+// (G after the wetting rotation, from the step's normal field)
+// block `block` of the `blocks` of particle p
+__device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, int p, int block,
+                                              int blocks) {
+  DevParticle& P = s.P[p];
+  const int B = s.cap_B;
+  int org[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) org[k] = (int)floor(P.x[k] - P.R);
+  if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
+  float4* box = s.capbox + (long long)p * B * B * B;
+  // the record's fields held in registers (the box stores may alias the record)
+  const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
+  const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd ^ 1]) + N;
+  const GLB float* __restrict__ NRM = gp((const float*)s.nrm);
+  const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
+  // a particle whose box holds no fluid node with |G| near EPS_G or above gets
+  // no force: every point's G is a convex combination of corner values, so it
+  // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
+  // rounding); the box's nodes say so here, once, for that kernel
+  bool iface = false;
+  for (int k = block * 256 + (int)threadIdx.x; k < B * B * B; k += blocks * 256) {
+    const int ix = k % B, iy = (k / B) % B, iz = k / (B * B);
+    const int x = wrapi(org[0] + ix, nx), y = wrapi(org[1] + iy, ny), z = wrapi(org[2] + iz, nz);
+    const unsigned n = (unsigned)(x + nx * (y + ny * z));
+    // every plane read at once and the solid case taken by selects (a load
+    // used only inside a branch is made there, a second round trip)
+    const float gw = at(NRM + 3 * N, n), ph = at(PHI, n);
+    const float n0 = at(NRM, n), n1 = at(NRM + N, n), n2 = at(NRM + 2 * N, n);
+    const uint8_t kind = KIND[kind_index(s, x, y, z)];
+    // G = n max(|G|, EPS_G): the colour gradient after the wetting rotation;
+    // phi = 2 marks a solid node; on a pure tile plane G is zero and its
+    // normal planes are not looked at
+    const bool fl = !(ph > PHI_SOLID_TEST), mixed = fl && kind == KIND_MIXED;
+    const float gm = fmaxf(gw, EPS_G);
+    const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
+                                 mixed ? n2 * gm : 0.f);
+    box[k] = v;
+    iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
+  }
+  if (__syncthreads_or(iface) && threadIdx.x == 0) P.cap_on = 1;
+}
+
 // ------------------------------------------------------------- fused kernel
 // Per fluid node (one thread, x-fastest): populations in, the paper's collision
 // on the total f (MRT + Guo forcing; the printed relaxation vector gives omega
@@ -1012,17 +1056,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 // k_links.
 // OPEN: the batch has simulations with open x ends (their anti-bounce-back is
 // compiled into this instance only).
+// FP32: cap_rows x cap_blocks blocks in front fill the particles' capillary boxes,
+// which read the normals as this kernel does and are summed beside k_links.
 template <int STORE, int MODE, bool OPEN>
 // six waves per SIMD: the FP16 instance fits 80 VGPRs without spills (it took
 // 85 and five waves; eight waves spill and nearly double its time); the FP32
 // instances need fewer anyway
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_fused(Batch bt, float* __restrict__ out_rho,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_fused(Batch bt, int cap_rows,
+                                              int cap_blocks, float* __restrict__ out_rho,
                                               float* __restrict__ out_u,
                                               float* __restrict__ out_phi,
                                               float* __restrict__ out_F) {
   using IO = Codec<STORE>;
   using T = typename IO::T;
-  const int2 sb = batch_block(bt, xcd_tile(blockIdx.x, gridDim.x));
+  // (in FP16 zero, but by its arguments: as a constant the instance spills)
+  const int first = MODE == MODE_STEP ? cap_rows * cap_blocks : 0;
+  if (STORE == 0 && (int)blockIdx.x < first) {
+    const int row = (int)blockIdx.x / cap_blocks;
+    const int2 cp = batch_particle(bt, row);
+    capillary_box(bt, bt.tab[cp.x], cp.y, (int)blockIdx.x - row * cap_blocks, cap_blocks);
+    return;
+  }
+  const int2 sb = batch_block(bt, xcd_tile((int)blockIdx.x - first, (int)gridDim.x - first));
   const SimDev& s = bt.tab[sb.x];
   const GLB T* __restrict__ sp_ = gp((const T*)s.pops[bt.cur]);
   GLB T* __restrict__ dp_ = gp((T*)s.pops[bt.cur ^ 1]);
@@ -1193,46 +1248,140 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   }
 }
 
-// per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
-// (G after the wetting rotation, from the step's normal field)
-__device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, int p) {
-  DevParticle& P = s.P[p];
-  const int B = s.cap_B;
-  int org[3];
+// The capillary boxes of a batch in FP16: in the launch of k_fused their code costs
+// that instance, which fills its 80 VGPRs, a spill per node (582 -> 605 us in
+// 512x256x192 with 500 spheres, against 19 for this launch; with one sphere 4).
+__global__ __launch_bounds__(256) void k_capbox(Batch bt) {
+  const int2 cp = batch_particle(bt, (int)blockIdx.y);
+  capillary_box(bt, bt.tab[cp.x], cp.y, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// Six sums over the threads of a block of 256: true, with the sum in v, for
+// thread c < 6 of component c.
+__device__ __forceinline__ bool block_sum6(double* acc, double (*red)[6], double& v) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) org[k] = (int)floor(P.x[k] - P.R);
+  for (int c = 0; c < 6; ++c)
+    for (int off = 32; off > 0; off >>= 1) acc[c] += __shfl_xor(acc[c], off, 64);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+    for (int c = 0; c < 6; ++c) red[wave][c] = acc[c];
+  __syncthreads();
+  if (threadIdx.x >= 6) return false;
+  v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
+  return true;
+}
+
+// Capillary force (capillary-force eq.): sum over the polar/azimuthal grid of
+// sigma 9/2 k beta max(0, 1 - phi^2) dA sin(theta_p) m^, m^ = normalise(n_s - (n.n_s) n),
+// torque arm R n_s; phi and G trilinear over fluid corners, from the box that
+// k_fused's launch filled.  Block `block` of the `blocks` of a particle, FP64 block
+// reductions combined with FP64 atomics (the accumulators are consumed and cleared
+// by the DEM).
+constexpr int CAP_TAB = 512;
+struct CapLds {
+  double tab[4][CAP_TAB];
+  double red[4][6];
+};
+__device__ __forceinline__ void capillary_block(const SimDev& s, int p, int block, int blocks,
+                                                CapLds& lds) {
+  DevParticle& P = s.P[p];
   if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
-  float4* box = s.capbox + (long long)p * B * B * B;
-  // the record's fields held in registers (the box stores may alias the record)
-  const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
-  const GLB float* __restrict__ PHI = gp((const float*)s.rp[bt.rd ^ 1]) + N;
-  const GLB float* __restrict__ NRM = gp((const float*)s.nrm);
-  const GLB uint8_t* __restrict__ KIND = gp((const uint8_t*)s.kind);
-  // a particle whose box holds no fluid node with |G| near EPS_G or above gets
-  // no force: every point's G is a convex combination of corner values, so it
-  // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
-  // rounding); the box's nodes say so here, once, for that kernel
-  bool iface = false;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < B * B * B; k += gridDim.x * blockDim.x) {
-    const int ix = k % B, iy = (k / B) % B, iz = k / (B * B);
-    const int x = wrapi(org[0] + ix, nx), y = wrapi(org[1] + iy, ny), z = wrapi(org[2] + iz, nz);
-    const unsigned n = (unsigned)(x + nx * (y + ny * z));
-    // every plane read at once and the solid case taken by selects (a load
-    // used only inside a branch is made there, a second round trip)
-    const float gw = at(NRM + 3 * N, n), ph = at(PHI, n);
-    const float n0 = at(NRM, n), n1 = at(NRM + N, n), n2 = at(NRM + 2 * N, n);
-    const uint8_t kind = KIND[kind_index(s, x, y, z)];
-    // G = n max(|G|, EPS_G): the colour gradient after the wetting rotation;
-    // phi = 2 marks a solid node; on a pure tile plane G is zero and its
-    // normal planes are not looked at
-    const bool fl = !(ph > PHI_SOLID_TEST), mixed = fl && kind == KIND_MIXED;
-    const float gm = fmaxf(gw, EPS_G);
-    const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
-                                 mixed ? n2 * gm : 0.f);
-    box[k] = v;
-    iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
+  const int B = s.cap_B;
+  const GLB v4f* box = gp((const v4f*)s.capbox) + (long long)p * B * B * B;
+  const int org0 = (int)floor(P.x[0] - P.R), org1 = (int)floor(P.x[1] - P.R),
+            org2 = (int)floor(P.x[2] - P.R);
+  const double R = P.R, da = s.cap_dang;
+  const double pref = s.cap_pref * (double)P.sin_t;
+  const int na = s.cap_na, nph = s.cap_nphi;
+  // the polar and azimuthal grids are fixed: their sines and cosines once per
+  // workgroup (same arguments, same values as per point)
+  // no fluid node of the box near the interface (the box kernel's flag): no force
+  if (!P.cap_on) return;
+  constexpr int TAB = CAP_TAB;
+  double *t_sa = lds.tab[0], *t_ca = lds.tab[1], *t_sp = lds.tab[2], *t_cp = lds.tab[3];
+  const bool tab = na <= TAB && nph <= TAB;
+  if (tab) {
+    for (int j = threadIdx.x; j < na; j += blockDim.x) sincos((j + 0.5) * da, &t_sa[j], &t_ca[j]);
+    for (int k = threadIdx.x; k < nph; k += blockDim.x) sincos(k * da, &t_sp[k], &t_cp[k]);
   }
-  if (__syncthreads_or(iface) && threadIdx.x == 0) P.cap_on = 1;
+  __syncthreads();
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int idx = block * 256 + (int)threadIdx.x; idx < na * nph; idx += blocks * 256) {
+    const int j = idx / nph, k = idx % nph;
+    double sa, ca, sp, cp;
+    if (tab) {
+      sa = t_sa[j];
+      ca = t_ca[j];
+      sp = t_sp[k];
+      cp = t_cp[k];
+    } else {
+      sincos((j + 0.5) * da, &sa, &ca);
+      sincos(k * da, &sp, &cp);
+    }
+    const double sh[3] = {sa * cp, sa * sp, ca};
+    const double xp[3] = {P.x[0] + R * sh[0], P.x[1] + R * sh[1], P.x[2] + R * sh[2]};
+    const double f0 = floor(xp[0]), f1 = floor(xp[1]), f2 = floor(xp[2]);
+    const double fr0 = xp[0] - f0, fr1 = xp[1] - f1, fr2 = xp[2] - f2;
+    const int i0 = (int)f0 - org0, i1 = (int)f1 - org1, i2 = (int)f2 - org2;
+    // per-point arithmetic in FP64: the torque is a small residual of large,
+    // cancelling per-point moments
+    double W = 0.0, phi = 0.0, Gx = 0.0, Gy = 0.0, Gz = 0.0;
+    // the eight corners loaded at once; a solid corner (phi = 2) takes weight
+    // 0, which adds exact zeros (the box holds finite values): the same sums as
+    // leaving it out, without a load round trip per corner
+    v4f cv[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int ox = c & 1, oy = (c >> 1) & 1, oz = c >> 2;
+      cv[c] = box[(i0 + ox) + B * ((i1 + oy) + B * (i2 + oz))];
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int ox = c & 1, oy = (c >> 1) & 1, oz = c >> 2;
+      const v4f v = cv[c];
+      const double w = (ox ? fr0 : 1.0 - fr0) * (oy ? fr1 : 1.0 - fr1) * (oz ? fr2 : 1.0 - fr2);
+      const double wf = v.x > 1.5f ? 0.0 : w;
+      W += wf;
+      phi += wf * (double)v.x;
+      Gx += wf * (double)v.y;
+      Gy += wf * (double)v.z;
+      Gz += wf * (double)v.w;
+    }
+    // the three tests at once, after the values they need (W = 0 gives NaN,
+    // which fails them): a test on W and phi alone before G is formed would let
+    // the compiler load the corners' G only after it, a second round trip
+    const double iW = 1.0 / W;
+    phi *= iW;
+    Gx *= iW;
+    Gy *= iW;
+    Gz *= iW;
+    const double wgt = 1.0 - phi * phi;
+    const double g = sqrt(Gx * Gx + Gy * Gy + Gz * Gz);
+    if (!(W > 0.0) || !(wgt > 0.0) || !(g > (double)EPS_G)) continue;
+    const double ig = 1.0 / g;
+    const double nx_ = Gx * ig, ny_ = Gy * ig, nz_ = Gz * ig;
+    const double a = nx_ * sh[0] + ny_ * sh[1] + nz_ * sh[2];
+    const double mx = sh[0] - a * nx_, my = sh[1] - a * ny_, mz = sh[2] - a * nz_;
+    const double mn = sqrt(mx * mx + my * my + mz * mz);
+    if (!(mn > (double)EPS_T)) continue;
+    const double dA = R * R * sa * da * da;
+    const double coef = pref * wgt * dA / mn;
+    const double dF[3] = {coef * mx, coef * my, coef * mz};
+    const double arm[3] = {R * sh[0], R * sh[1], R * sh[2]};
+    acc[0] += dF[0];
+    acc[1] += dF[1];
+    acc[2] += dF[2];
+    acc[3] += arm[1] * dF[2] - arm[2] * dF[1];
+    acc[4] += arm[2] * dF[0] - arm[0] * dF[2];
+    acc[5] += arm[0] * dF[1] - arm[1] * dF[0];
+  }
+  double v;
+  if (block_sum6(acc, lds.red, v)) {
+    if (threadIdx.x < 3)
+      atomicAdd(&P.Fca[threadIdx.x], v);
+    else
+      atomicAdd(&P.Tca[threadIdx.x - 3], v);
+  }
 }
 
 // Moving-wall correction and momentum exchange on particle links, after
@@ -1243,16 +1392,15 @@ __device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, 
 // momentum given to the particle dP = (c_i - u_w) f*_i - (c_opp - u_w) f_opp
 // (hydrodynamic force eqs.), summed in FP64 per particle.  One grid row per
 // particle over the nodes of its bounding box grown by one; with capillary
-// forces a second row per particle fills its capillary box, which needs nothing
-// of the first (both wait on memory: 66 + 21 -> 70 us with 500 spheres, 11 + 4
-// -> 11 us with one).
+// forces the row's blocks from link_blocks on sum those, which need nothing of the
+// others (the dependent chains of both hide each other's: one sphere 11.5 + 8 -> 11 us, 20
+// spheres 14 + 5 -> 15.7, 500 spheres 77 + 25 -> 81).
 template <int STORE>
-__global__ __launch_bounds__(256) void k_links(Batch bt, int np_rows) {
-  if ((int)blockIdx.y >= np_rows) {
-    const int2 cp = batch_particle(bt, (int)blockIdx.y - np_rows);
-    capillary_box(bt, bt.tab[cp.x], cp.y);
-    return;
-  }
+__global__ __launch_bounds__(256) void k_links(Batch bt, int link_blocks) {
+  __shared__ union {
+    double red[4][6];
+    CapLds cap;
+  } u;
   // one thread per node of the particle's box; runs after k_fused, before the
   // buffers swap: src holds the state it read, dst the state it wrote
   using IO = Codec<STORE>;
@@ -1260,6 +1408,10 @@ __global__ __launch_bounds__(256) void k_links(Batch bt, int np_rows) {
   const int2 sp = batch_particle(bt, blockIdx.y);
   const SimDev& s = bt.tab[sp.x];
   const int p = sp.y;
+  if ((int)blockIdx.x >= link_blocks) {
+    capillary_block(s, p, (int)blockIdx.x - link_blocks, (int)gridDim.x - link_blocks, u.cap);
+    return;
+  }
   GLB T* __restrict__ dp_ = gp((T*)s.pops[bt.cur ^ 1]);
   // moments of the state that collided: rho(x), and the FP16 reference of the
   // populations k_fused wrote
@@ -1350,25 +1502,13 @@ __global__ __launch_bounds__(256) void k_links(Batch bt, int np_rows) {
     }
   }
   if (!__syncthreads_or(any)) return;  // no link in this block
-  // wave reduction, then across the block's waves
-#pragma unroll
-  for (int c = 0; c < 6; ++c)
-    for (int off = 32; off > 0; off >>= 1) acc[c] += __shfl_xor(acc[c], off, 64);
-  __shared__ double red[4][6];
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int c = 0; c < 6; ++c) red[wave][c] = acc[c];
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    const double v = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] +
-                     red[3][threadIdx.x];
-    if (v != 0.0) {
-      DevParticle* Pw = s.P + p;
-      if (threadIdx.x < 3)
-        atomicAdd(&Pw->Fh[threadIdx.x], v);
-      else
-        atomicAdd(&Pw->Th[threadIdx.x - 3], v);
-    }
+  double v;
+  if (block_sum6(acc, u.red, v) && v != 0.0) {
+    DevParticle* Pw = s.P + p;
+    if (threadIdx.x < 3)
+      atomicAdd(&Pw->Fh[threadIdx.x], v);
+    else
+      atomicAdd(&Pw->Th[threadIdx.x - 3], v);
   }
 }
 
@@ -1395,43 +1535,65 @@ hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int mode, float* orho,
-                        float* ou, float* ophi, float* oF, hipStream_t st) {
-  const dim3 grid(nblk);
-  // the fields pass writes no populations: it needs no open-end instance
-  if (mode != MODE_STEP) {
-    if (storage == 0)
-      hipLaunchKernelGGL((k_fused<0, MODE_FIELDS, false>), grid, dim3(256), 0, st, b, orho, ou,
-                         ophi, oF);
-    else
-      hipLaunchKernelGGL((k_fused<1, MODE_FIELDS, false>), grid, dim3(256), 0, st, b, orho, ou,
-                         ophi, oF);
-  } else if (storage == 0) {
+// cap_rows particle rows (0: none) fill their capillary boxes of at most Bcap nodes
+// a side, in a step
+hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows, int Bcap,
+                        hipStream_t st) {
+  const int cap_blocks = (int)nblocks((long long)Bcap * Bcap * Bcap, 256);
+  const dim3 t(256);
+  float* const no = nullptr;
+  if (storage == 0) {
+    const dim3 grid(nblk + (unsigned)(cap_rows * cap_blocks));
     if (b.open)
-      hipLaunchKernelGGL((k_fused<0, MODE_STEP, true>), grid, dim3(256), 0, st, b, orho, ou, ophi, oF);
+      hipLaunchKernelGGL((k_fused<0, MODE_STEP, true>), grid, t, 0, st, b, cap_rows, cap_blocks, no,
+                         no, no, no);
     else
-      hipLaunchKernelGGL((k_fused<0, MODE_STEP, false>), grid, dim3(256), 0, st, b, orho, ou, ophi, oF);
+      hipLaunchKernelGGL((k_fused<0, MODE_STEP, false>), grid, t, 0, st, b, cap_rows, cap_blocks,
+                         no, no, no, no);
   } else {
+    if (cap_rows > 0)
+      hipLaunchKernelGGL(k_capbox, dim3((unsigned)cap_blocks, (unsigned)cap_rows), t, 0, st, b);
     if (b.open)
-      hipLaunchKernelGGL((k_fused<1, MODE_STEP, true>), grid, dim3(256), 0, st, b, orho, ou, ophi, oF);
+      hipLaunchKernelGGL((k_fused<1, MODE_STEP, true>), dim3(nblk), t, 0, st, b, 0, 0, no, no, no,
+                         no);
     else
-      hipLaunchKernelGGL((k_fused<1, MODE_STEP, false>), grid, dim3(256), 0, st, b, orho, ou, ophi, oF);
+      hipLaunchKernelGGL((k_fused<1, MODE_STEP, false>), dim3(nblk), t, 0, st, b, 0, 0, no, no, no,
+                         no);
   }
   return hipGetLastError();
 }
 
-// cap: fill the capillary boxes too
-hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, bool cap,
+// the fields of the current state, written where a pointer is given; it writes no
+// populations and needs no open-end instance
+hipError_t launch_fields(const Batch& b, int storage, unsigned nblk, float* orho, float* ou,
+                         float* ophi, float* oF, hipStream_t st) {
+  const dim3 grid(nblk), t(256);
+  if (storage == 0)
+    hipLaunchKernelGGL((k_fused<0, MODE_FIELDS, false>), grid, t, 0, st, b, 0, 0, orho, ou, ophi,
+                       oF);
+  else
+    hipLaunchKernelGGL((k_fused<1, MODE_FIELDS, false>), grid, t, 0, st, b, 0, 0, orho, ou, ophi,
+                       oF);
+  return hipGetLastError();
+}
+
+// npts: Lagrangian points per particle, 0: no capillary forces
+hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, int npts,
                         hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
-  // the box of k_links spans at most 2 R + 6 nodes per axis, R <= (Bmask - 5) / 2,
-  // the capillary box fewer
+  // the box of k_links spans at most 2 R + 6 nodes per axis, R <= (Bmask - 5) / 2
   const long long B = Bmax + 1;
-  const dim3 grid((unsigned)((B * B * B + 255) / 256), cap ? 2 * np_rows : np_rows);
+  const unsigned nl = nblocks(B * B * B, 256);
+  // workgroups per particle: four points per thread, or down to one where
+  // few particles leave the GPU idle (about 2,048 workgroups in all)
+  const int wide = std::min(npts / 256, (2048 + np_rows - 1) / np_rows);
+  const int many = std::max(1, (4096 + np_rows - 1) / np_rows);
+  const int split = std::max(1, std::min(64, std::max(std::min(npts / (256 * 4), many), wide)));
+  const dim3 grid(nl + (npts > 0 ? split : 0), np_rows);
   if (storage == 0)
-    hipLaunchKernelGGL(k_links<0>, grid, dim3(256), 0, st, b, np_rows);
+    hipLaunchKernelGGL(k_links<0>, grid, dim3(256), 0, st, b, (int)nl);
   else
-    hipLaunchKernelGGL(k_links<1>, grid, dim3(256), 0, st, b, np_rows);
+    hipLaunchKernelGGL(k_links<1>, grid, dim3(256), 0, st, b, (int)nl);
   return hipGetLastError();
 }
 

@@ -154,124 +154,6 @@ __global__ __launch_bounds__(256) void k_mask(Batch bt) {
   if (in && m == 0 && owner(x, y, z) == p) MASK[n] = (uint16_t)(2 + p);
 }
 
-// -------------------------------------------------------------- capillary
-// Capillary force (capillary-force eq.): sum over the polar/azimuthal grid of
-// sigma 9/2 k beta max(0, 1 - phi^2) dA sin(theta_p) m^, m^ = normalise(n_s - (n.n_s) n),
-// torque arm R n_s; phi and G trilinear over fluid corners.  A grid row of
-// workgroups per particle, FP64 block reductions combined with FP64 atomics
-// (the accumulators are consumed and cleared by the DEM).
-__global__ __launch_bounds__(256) void k_capillary(Batch bt) {
-  const int2 sp = batch_particle(bt, blockIdx.y);
-  const SimDev& s = bt.tab[sp.x];
-  const int p = sp.y;
-  DevParticle& P = s.P[p];
-  if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
-  const int B = s.cap_B;
-  const GLB v4f* box = gp((const v4f*)s.capbox) + (long long)p * B * B * B;
-  const int org0 = (int)floor(P.x[0] - P.R), org1 = (int)floor(P.x[1] - P.R),
-            org2 = (int)floor(P.x[2] - P.R);
-  const double R = P.R, da = s.cap_dang;
-  const double pref = s.cap_pref * (double)P.sin_t;
-  const int na = s.cap_na, nph = s.cap_nphi;
-  // the polar and azimuthal grids are fixed: their sines and cosines once per
-  // workgroup (same arguments, same values as per point)
-  // no fluid node of the box near the interface (the box kernel's flag): no force
-  if (!P.cap_on) return;
-  constexpr int TAB = 512;
-  __shared__ double t_sa[TAB], t_ca[TAB], t_sp[TAB], t_cp[TAB];
-  const bool tab = na <= TAB && nph <= TAB;
-  if (tab) {
-    for (int j = threadIdx.x; j < na; j += blockDim.x) sincos((j + 0.5) * da, &t_sa[j], &t_ca[j]);
-    for (int k = threadIdx.x; k < nph; k += blockDim.x) sincos(k * da, &t_sp[k], &t_cp[k]);
-  }
-  __syncthreads();
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < na * nph;
-       idx += gridDim.x * blockDim.x) {
-    const int j = idx / nph, k = idx % nph;
-    double sa, ca, sp, cp;
-    if (tab) {
-      sa = t_sa[j];
-      ca = t_ca[j];
-      sp = t_sp[k];
-      cp = t_cp[k];
-    } else {
-      sincos((j + 0.5) * da, &sa, &ca);
-      sincos(k * da, &sp, &cp);
-    }
-    const double sh[3] = {sa * cp, sa * sp, ca};
-    const double xp[3] = {P.x[0] + R * sh[0], P.x[1] + R * sh[1], P.x[2] + R * sh[2]};
-    const double f0 = floor(xp[0]), f1 = floor(xp[1]), f2 = floor(xp[2]);
-    const double fr0 = xp[0] - f0, fr1 = xp[1] - f1, fr2 = xp[2] - f2;
-    const int i0 = (int)f0 - org0, i1 = (int)f1 - org1, i2 = (int)f2 - org2;
-    // per-point arithmetic in FP64: the torque is a small residual of large,
-    // cancelling per-point moments
-    double W = 0.0, phi = 0.0, Gx = 0.0, Gy = 0.0, Gz = 0.0;
-    // the eight corners loaded at once; a solid corner (phi = 2) takes weight
-    // 0, which adds exact zeros (the box holds finite values): the same sums as
-    // leaving it out, without a load round trip per corner
-    v4f cv[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int ox = c & 1, oy = (c >> 1) & 1, oz = c >> 2;
-      cv[c] = box[(i0 + ox) + B * ((i1 + oy) + B * (i2 + oz))];
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int ox = c & 1, oy = (c >> 1) & 1, oz = c >> 2;
-      const v4f v = cv[c];
-      const double w = (ox ? fr0 : 1.0 - fr0) * (oy ? fr1 : 1.0 - fr1) * (oz ? fr2 : 1.0 - fr2);
-      const double wf = v.x > 1.5f ? 0.0 : w;
-      W += wf;
-      phi += wf * (double)v.x;
-      Gx += wf * (double)v.y;
-      Gy += wf * (double)v.z;
-      Gz += wf * (double)v.w;
-    }
-    // the three tests at once, after the values they need (W = 0 gives NaN,
-    // which fails them): a test on W and phi alone before G is formed would let
-    // the compiler load the corners' G only after it, a second round trip
-    const double iW = 1.0 / W;
-    phi *= iW;
-    Gx *= iW;
-    Gy *= iW;
-    Gz *= iW;
-    const double wgt = 1.0 - phi * phi;
-    const double g = sqrt(Gx * Gx + Gy * Gy + Gz * Gz);
-    if (!(W > 0.0) || !(wgt > 0.0) || !(g > (double)EPS_G)) continue;
-    const double ig = 1.0 / g;
-    const double nx_ = Gx * ig, ny_ = Gy * ig, nz_ = Gz * ig;
-    const double a = nx_ * sh[0] + ny_ * sh[1] + nz_ * sh[2];
-    const double mx = sh[0] - a * nx_, my = sh[1] - a * ny_, mz = sh[2] - a * nz_;
-    const double mn = sqrt(mx * mx + my * my + mz * mz);
-    if (!(mn > (double)EPS_T)) continue;
-    const double dA = R * R * sa * da * da;
-    const double coef = pref * wgt * dA / mn;
-    const double dF[3] = {coef * mx, coef * my, coef * mz};
-    const double arm[3] = {R * sh[0], R * sh[1], R * sh[2]};
-    acc[0] += dF[0];
-    acc[1] += dF[1];
-    acc[2] += dF[2];
-    acc[3] += arm[1] * dF[2] - arm[2] * dF[1];
-    acc[4] += arm[2] * dF[0] - arm[0] * dF[2];
-    acc[5] += arm[0] * dF[1] - arm[1] * dF[0];
-  }
-  __shared__ double red[6][256];
-  for (int k = 0; k < 6; ++k) red[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      for (int k = 0; k < 6; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    for (int k = 0; k < 3; ++k) {
-      atomicAdd(&P.Fca[k], red[k][0]);
-      atomicAdd(&P.Tca[k], red[3 + k][0]);
-    }
-  }
-}
-
 // -------------------------------------------------------------------- DEM
 __device__ inline void cross3(const double* a, const double* b, double* o) {
   o[0] = a[1] * b[2] - a[2] * b[1];
@@ -1143,18 +1025,6 @@ hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_r
     hipLaunchKernelGGL(k_mask<true>, grid, dim3(256), 0, st, b);
   else
     hipLaunchKernelGGL(k_mask<false>, grid, dim3(256), 0, st, b);
-  return hipGetLastError();
-}
-
-// npts: Lagrangian points per particle
-hipError_t launch_capillary(const Batch& b, int np_rows, int npts, hipStream_t st) {
-  if (np_rows == 0) return hipSuccess;
-  // workgroups per particle: four points per thread, or down to one where
-  // few particles leave the GPU idle (about 2,048 workgroups in all)
-  const int wide = std::min(npts / 256, (2048 + np_rows - 1) / np_rows);
-  const int many = std::max(1, (4096 + np_rows - 1) / np_rows);
-  const unsigned split = (unsigned)std::max(1, std::min(64, std::max(std::min(npts / (256 * 4), many), wide)));
-  hipLaunchKernelGGL(k_capillary, dim3(split, np_rows), dim3(256), 0, st, b);
   return hipGetLastError();
 }
 
