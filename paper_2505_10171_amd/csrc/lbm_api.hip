@@ -437,25 +437,24 @@ static void default_marches(std::vector<SimHost>& sims) {
   default_march(sims, false);
 }
 
-// open x ends, a tube or a textured wall: the interface kernel's general
-// instance; open x ends: the fused kernel's
-static int general_geometry(const lbm_config& c) {
-  return c.open_x || c.has_wall == LBM_WALL_TUBE || c.has_wall == LBM_WALL_BOXES;
+static int geometry_of(const lbm_config& c) {
+  if (c.has_wall == LBM_WALL_BOXES) return GEO_BOXES;
+  return c.open_x || c.has_wall == LBM_WALL_TUBE ? GEO_TUBE : GEO_PLAIN;
 }
 static Batch batch_all(const lbm_ctx* c) {
-  int general = 0, open = 0;
+  int geometry = GEO_PLAIN, open = 0;
   int mlx = c->sims.empty() ? 0 : c->sims[0].d.mtile_lx;
   for (const SimHost& sh : c->sims) {
-    general |= general_geometry(sh.cfg);
+    geometry = std::max(geometry, geometry_of(sh.cfg));
     open |= sh.cfg.open_x;
     if (sh.d.mtile_lx != mlx) mlx = 0;
   }
   return Batch{c->d_tab, c->d_blk, c->d_mblk, c->d_pmap, (int)c->sims.size(), c->cur, c->rd,
-               general, open, mlx, 0, 0};
+               geometry, open, mlx, 0, 0};
 }
 static Batch batch_one(const lbm_ctx* c, int si) {
   return Batch{c->d_tab + si, nullptr, nullptr, nullptr, 1, c->cur, c->rd,
-               general_geometry(c->sims[si].cfg), c->sims[si].cfg.open_x,
+               geometry_of(c->sims[si].cfg), c->sims[si].cfg.open_x,
                c->sims[si].d.mtile_lx, c->sims[si].solo, 0};
 }
 

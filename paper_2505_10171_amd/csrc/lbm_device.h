@@ -317,6 +317,10 @@ __host__ __device__ inline bool near_open_end(const SimDev& s, double x, double 
   return s.open_x && (x < R + 4.0 || x > (double)(s.nx - 1) - R - 4.0);
 }
 
+// What the interface kernel of a batch has to know: nothing but planes and
+// particles; open x ends or a tube wall too; textured walls as well.
+enum Geometry { GEO_PLAIN = 0, GEO_TUBE = 1, GEO_BOXES = 2 };
+
 // One launch covers a batch of simulations (an ensemble, or a single one).
 // Per-node kernels run 256-node blocks; blk[s] is the first global block of
 // simulation s (blk[nsim] the total).  Particle kernels run one grid row per
@@ -331,7 +335,7 @@ struct Batch {
   const int2* pmap;
   int nsim;
   int cur, rd;
-  int general;  // some simulation has open x ends, a tube or a textured wall
+  int geometry;  // the largest Geometry of its simulations
   int open;     // some simulation has open x ends
   int mlx;      // log2 of the moments tiles' x width if every simulation has the same, else 0
   int mkz;      // marching depth of this launch, 0: each simulation's own

@@ -30,8 +30,8 @@ namespace lbm {
 // Between those thresholds and twice their value the rotated vector is blended
 // in with weight w = min(1, |t|/EPS_GT - 1) min(1, |G|/EPS_G - 1), so that G is
 // continuous in phi (no last-bit difference can switch the rotation on or off).
-// GENERAL: the tube's wall normal is compiled in.
-template <bool GENERAL = true>
+// GEO: the geometries compiled in (Geometry).
+template <int GEO>
 __device__ __forceinline__ void wetting_rotate(const SimDev& s, int gx, int gy, int gz, int minp,
                                                bool wall_nb, float& Gx, float& Gy, float& Gz) {
   float g = sqrtf(Gx * Gx + Gy * Gy + Gz * Gz);
@@ -50,47 +50,45 @@ __device__ __forceinline__ void wetting_rotate(const SimDev& s, int gx, int gy, 
     nsz = (float)(dz * idn);
     nc = P.neg_cos_t;
     ns = P.sin_t;
-  } else if (wall_nb && (!GENERAL || s.has_wall == 1)) {
+  } else if (wall_nb && (GEO == GEO_PLAIN || s.has_wall == 1)) {
     nsx = 0.f;
     nsy = 0.f;
     nsz = (gz == 1) ? 1.f : -1.f;
     nc = s.wall_neg_cos;
     ns = s.wall_sin;
-  } else if (wall_nb && s.has_wall == 3) {
+  } else if (GEO == GEO_BOXES && wall_nb && s.has_wall == 3) {
     // textured wall: the normal of the nearest point of the solid surface (the
     // plane's top face z = 1/2, or its underside z = nz - 1/2 through the
     // periodic z direction; the boxes grown by half a node), from it to the
     // node; on ties the plane, then the lowest box index
-    // (distances compared squared: node and surface coordinates are
-    // multiples of 1/2, so the squares are exact; one square root, for the
-    // winner)
-    const double dt = (double)gz - 0.5, du = ((double)s.nz - 0.5) - (double)gz;
-    const double dp = dt <= du ? dt : du;
-    double best2 = dp * dp;
-    double bx = 0.0, by = 0.0, bz = dt <= du ? 1.0 : -1.0;
-    bool boxed = false;
-    for (int b = 0; b < s.n_boxes; ++b) {
+    // (in half nodes all coordinates are whole numbers: distances are compared
+    // squared and exact, in integers; one square root, for the winner)
+    const int hx = 2 * gx, hy = 2 * gy, hz = 2 * gz;
+    const int dt = hz - 1, du = (2 * s.nz - 1) - hz;
+    const int dp = min(dt, du);
+    long long best2 = (long long)dp * dp;
+    int b0 = 0, b1 = 0, b2 = 0;
+    const int n_boxes = s.n_boxes;
+    for (int b = 0; b < n_boxes; ++b) {
       const int* B = s.boxes[b];
-      const double p[3] = {(double)gx, (double)gy, (double)gz};
-      double d[3];
-      for (int k = 0; k < 3; ++k) {
-        const double lo = B[k] - 0.5, hi = B[3 + k] + 0.5;
-        d[k] = p[k] - (p[k] < lo ? lo : (p[k] > hi ? hi : p[k]));
-      }
-      const double d2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-      if (d2 > 0.0 && d2 < best2) {
-        best2 = d2;
-        bx = d[0];
-        by = d[1];
-        bz = d[2];
-        boxed = true;
+      // beyond the upper face, before the lower one, or 0 between them
+      const int d0 = max(hx - (2 * B[3] + 1), 0) + min(hx - (2 * B[0] - 1), 0);
+      const int d1 = max(hy - (2 * B[4] + 1), 0) + min(hy - (2 * B[1] - 1), 0);
+      const int d2 = max(hz - (2 * B[5] + 1), 0) + min(hz - (2 * B[2] - 1), 0);
+      const long long dd = (long long)d0 * d0 + (long long)d1 * d1 + (long long)d2 * d2;
+      if (dd > 0 && dd < best2) {
+        best2 = dd;
+        b0 = d0;
+        b1 = d1;
+        b2 = d2;
       }
     }
-    if (boxed) {
-      const double idn = 1.0 / sqrt(best2);
-      bx *= idn;
-      by *= idn;
-      bz *= idn;
+    double bx = 0.0, by = 0.0, bz = dt <= du ? 1.0 : -1.0;
+    if ((b0 | b1 | b2) != 0) {
+      const double idn = 1.0 / sqrt(0.25 * (double)best2);
+      bx = 0.5 * (double)b0 * idn;
+      by = 0.5 * (double)b1 * idn;
+      bz = 0.5 * (double)b2 * idn;
     }
     nsx = (float)bx;
     nsy = (float)by;
@@ -598,21 +596,25 @@ enum { MODE_STEP = 0, MODE_FIELDS = 1 };
 // normals never travel to HBM and back between the two stencils.
 constexpr int IF_PHI = 68 * 8;          // largest tile plane grown by two: (64 + 4)(4 + 4)
 constexpr int IF_NRM = MOM_HALO;  // grown by one: (64 + 2)(4 + 2)
-// OPEN: the batch has simulations with open x ends or a tube wall (a
-// separate instance, so that the periodic box on a plane carries none of their
-// bookkeeping).
+// GEO: the geometries of the batch, so that the periodic box on a plane carries
+// none of the others' bookkeeping and a tube nothing of a textured wall's.
 // LX: as for the moments pass
 struct IfLds {
   float fring[4][IF_PHI];
   // normals of three planes, one array per component (the curvature reads
   // only the components its stencil direction needs); |G| only where the
   // curvature needs it, at the tile's own nodes
-  float nrx[3][IF_NRM], nry[3][IF_NRM], nrz[3][IF_NRM], nrg[3][256];
+  float nrx[3][IF_NRM], nry[3][IF_NRM], nrz[3][IF_NRM], nrg[2][256];
   uint32_t wcls[2][4];
+  // entries that the wetting rotation is still to turn: 2 planes at most
+  uint16_t wet[2 * IF_NRM];
+  uint32_t n_wet;
 };
-template <bool OPEN, int LX>
+static_assert(6 * sizeof(IfLds) <= 160 * 1024, "six blocks per CU");
+template <int GEO, int LX>
 __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s, const int2 sb,
                                                 IfLds& lds) {
+  constexpr bool OPEN = GEO != GEO_PLAIN;
   auto& fring = lds.fring;
   auto &nrx = lds.nrx, &nry = lds.nry, &nrz = lds.nrz;
   auto& nrg = lds.nrg;
@@ -668,6 +670,7 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
   auto zw = [&](int z) { return wrapi(z, nz); };
   auto fslot = [&](int z) { return (z + 8) & 3; };  // z >= -2
   auto nslot = [&](int z) { return (z + 3) % 3; };   // z >= -1
+  auto gslot = [&](int z) { return (z + 2) & 1; };   // z >= -1
   auto load_phi = [&](int z, float* v) {
     const int zp = zw(z);
 #pragma unroll
@@ -680,10 +683,23 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
       if (fon[j]) fring[fslot(z)][t + 256 * j] = v[j];
   };
   const float qnan = __int_as_float(0x7fc00000);
+  // G as a unit vector (or less, below EPS_G) and |G|
+  auto unit = [](float Gx, float Gy, float Gz) -> v4f {
+    const float g = sqrtf(Gx * Gx + Gy * Gy + Gz * Gz);
+    // 1 / max(g, EPS_G): the hardware reciprocal (within 1 ulp) and one Newton
+    // step, which leaves it within a hair of half an ulp (the divisor lies in
+    // [1e-4, 4], far from denormals and overflow); three instructions where the
+    // full division takes twelve
+    const float m = fmaxf(g, EPS_G);
+    const float r0 = __builtin_amdgcn_rcpf(m);
+    const float ig = __fmaf_rn(__fmaf_rn(-m, r0, 1.0f), r0, r0);
+    return v4f{Gx * ig, Gy * ig, Gz * ig, g};
+  };
   // normal of region entry (hx, hy) of plane z from the phi ring
   // SOL: a solid (or open-end) node may lie in the three phi planes read;
   // without, the per-neighbour tests are left out (a block-uniform choice)
-  auto normal = [&](int hx, int hy, int z, auto SOL) -> v4f {
+  // (an entry inside the interface with a solid neighbour: `wet`, G itself)
+  auto normal = [&](int hx, int hy, int z, bool& wet, auto SOL) -> v4f {
     const int c = (hx + 1) + FX * (hy + 1);
     const float* fm = fring[fslot(z - 1)];
     const float* f0 = fring[fslot(z)];
@@ -713,54 +729,90 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
       if (cy(i) != 0) Gy = __fmaf_rn((float)cy(i) * k, df, Gy);
       if (cz(i) != 0) Gz = __fmaf_rn((float)cz(i) * k, df, Gz);
     }
-    // the wetting rotation applies only inside the interface (|G| > EPS_G, its
-    // own first test); only there the solid is identified, from the phi
-    // codes of the neighbours in the ring: the lowest-index particle, else
-    // the wall (an open end is neither)
-    if (decltype(SOL)::value && solid && sqrtf(Gx * Gx + Gy * Gy + Gz * Gz) > EPS_G) {
-      float pmin = 3.0e38f;
-      bool wall = false;
+    v4f v = unit(Gx, Gy, Gz);
+    wet = decltype(SOL)::value && solid && v.w > EPS_G;
+    if (wet) v = v4f{Gx, Gy, Gz, v.w};
+    return v;
+  };
+  auto put_normal = [&](int hx, int hy, int z, v4f v) {
+    const int sl = nslot(z), k = hx + HX * hy;
+    nrx[sl][k] = v.x;
+    nry[sl][k] = v.y;
+    nrz[sl][k] = v.z;
+    // a tile node: its |G| kept for the curvature
+    const int tlx = hx - 1, tly = hy - 1;
+    if (tlx >= 0 && tlx < tx && tly >= 0 && tly < ty) nrg[gslot(z)][tlx + tx * tly] = v.w;
+  };
+  // The wetting rotation applies only inside the interface (|G| > EPS_G, its own
+  // first test); only there the solid is identified, from the phi codes of the
+  // neighbours in the ring: the lowest-index particle, else the wall (an open end
+  // is neither).
+  auto rotated = [&](int hx, int hy, int z, float Gx, float Gy, float Gz) -> v4f {
+    const int c = (hx + 1) + FX * (hy + 1);
+    const float* fm = fring[fslot(z - 1)];
+    const float* f0 = fring[fslot(z)];
+    const float* fp = fring[fslot(z + 1)];
+    float pmin = 3.0e38f;
+    bool wall = false;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        const int i = pair_dir(q);
-        const float* sp_ = cz(i) > 0 ? fp : (cz(i) < 0 ? fm : f0);
-        const float* sm_ = cz(i) > 0 ? fm : (cz(i) < 0 ? fp : f0);
-        const float vp = sp_[c + cx(i) + FX * cy(i)];
-        const float vm = sm_[c - cx(i) - FX * cy(i)];
-        wall |= vp == solid_phi(1) || vm == solid_phi(1);
-        if (vp >= solid_phi(2)) pmin = fminf(pmin, vp);
-        if (vm >= solid_phi(2)) pmin = fminf(pmin, vm);
+    for (int q = 0; q < 9; ++q) {
+      const int i = pair_dir(q);
+      const float* sp_ = cz(i) > 0 ? fp : (cz(i) < 0 ? fm : f0);
+      const float* sm_ = cz(i) > 0 ? fm : (cz(i) < 0 ? fp : f0);
+      const float vp = sp_[c + cx(i) + FX * cy(i)];
+      const float vm = sm_[c - cx(i) - FX * cy(i)];
+      wall |= vp == solid_phi(1) || vm == solid_phi(1);
+      if (vp >= solid_phi(2)) pmin = fminf(pmin, vp);
+      if (vm >= solid_phi(2)) pmin = fminf(pmin, vm);
+    }
+    if (wall || pmin < 3.0e38f) {
+      const int ax = wrapi(x0 - 1 + hx, nx), ay = wrapi(y0 - 1 + hy, ny), az = zw(z);
+      const int minp = pmin < 3.0e38f ? (int)(pmin - solid_phi(2)) : -1;
+      wetting_rotate<GEO>(s, ax, ay, az, minp, wall, Gx, Gy, Gz);
+    }
+    return unit(Gx, Gy, Gz);
+  };
+  // A few entries of a plane are rotated, and the chain is long (the scan, the
+  // particle's record from memory, square roots and divisions in FP64): they are
+  // queued, and all of up to two planes take it at once, a thread each.  Each
+  // thread for its own two entries as they came, a block passed the chain twice
+  // per plane (sphere of radius 10 in 32x32x52: 19.6 -> 14.7 us, a drop on pillars
+  // in 256x128x64 66 -> 43).  In a tube, where the rotated entries are those along
+  // the wall, a row of them in most waves, each thread's own stay the better (27
+  // us against 29 queued).
+  constexpr bool QUEUE = GEO != GEO_TUBE;
+  // up: 1 for the upper of two planes that are formed before rotate_wet
+  auto normals = [&](int z, int up, auto SOL) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bool wet = false;
+      if (hon[j]) {
+        v4f v = normal(hx_[j], hy_[j], z, wet, SOL);
+        if (decltype(SOL)::value && !QUEUE && wet) v = rotated(hx_[j], hy_[j], z, v.x, v.y, v.z);
+        put_normal(hx_[j], hy_[j], z, v);
       }
-      if (wall || pmin < 3.0e38f) {
-        const int ax = wrapi(x0 - 1 + hx, nx), ay = wrapi(y0 - 1 + hy, ny), az = zw(z);
-        const int minp = pmin < 3.0e38f ? (int)(pmin - solid_phi(2)) : -1;
-        wetting_rotate<OPEN>(s, ax, ay, az, minp, wall, Gx, Gy, Gz);
+      if constexpr (decltype(SOL)::value && QUEUE) {
+        // (the order is free; the compiler takes a wave's places at once)
+        if (wet)
+          lds.wet[atomicAdd(&lds.n_wet, 1u)] = (uint16_t)((hx_[j] + HX * hy_[j]) | (up << 15));
       }
     }
-    const float g = sqrtf(Gx * Gx + Gy * Gy + Gz * Gz);
-    // 1 / max(g, EPS_G): the hardware reciprocal (within 1 ulp) and one Newton
-    // step, which leaves it within a hair of half an ulp (the divisor lies in
-    // [1e-4, 4], far from denormals and overflow); three instructions where the
-    // full division takes twelve
-    const float m = fmaxf(g, EPS_G);
-    const float r0 = __builtin_amdgcn_rcpf(m);
-    const float ig = __fmaf_rn(__fmaf_rn(-m, r0, 1.0f), r0, r0);
-    return v4f{Gx * ig, Gy * ig, Gz * ig, g};
   };
-  auto normals = [&](int z, auto SOL) {
-    const int sl = nslot(z);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      if (hon[j]) {
-        const v4f v = normal(hx_[j], hy_[j], z, SOL);
-        const int k = hx_[j] + HX * hy_[j];
-        nrx[sl][k] = v.x;
-        nry[sl][k] = v.y;
-        nrz[sl][k] = v.z;
-        // a tile node: its |G| kept for the curvature
-        const int tlx = hx_[j] - 1, tly = hy_[j] - 1;
-        if (tlx >= 0 && tlx < tx && tly >= 0 && tly < ty) nrg[sl][tlx + tx * tly] = v.w;
+  // the queued entries of plane z (and, marked up, z + 1), between the barrier
+  // behind the normals and the one that this ends with
+  auto rotate_wet = [&](int z) {
+    if constexpr (QUEUE) {
+      const uint32_t n_wet = __builtin_amdgcn_readfirstlane(lds.n_wet);
+      if (n_wet == 0u) return;
+      for (uint32_t w = t; w < n_wet; w += 256) {
+        const uint32_t code = lds.wet[w];
+        const int k = (int)(code & 0x7fffu), hy = k / HX, hx = k - HX * hy;
+        const int zn = z + (int)(code >> 15), sl = nslot(zn);
+        put_normal(hx, hy, zn, rotated(hx, hy, zn, nrx[sl][k], nry[sl][k], nrz[sl][k]));
       }
+      __syncthreads();
+      if (t == 0) lds.n_wet = 0u;
+    }
   };
   const std::integral_constant<bool, true> with_solids;
   const std::integral_constant<bool, false> no_solids;
@@ -779,7 +831,8 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
         nry[sl][k] = v;
         nrz[sl][k] = v;
         const int tlx = hx_[j] - 1, tly = hy_[j] - 1;
-        if (tlx >= 0 && tlx < tx && tly >= 0 && tly < ty) nrg[sl][tlx + tx * tly] = sd ? -1.f : 0.f;
+        if (tlx >= 0 && tlx < tx && tly >= 0 && tly < ty)
+          nrg[gslot(z)][tlx + tx * tly] = sd ? -1.f : 0.f;
       }
   };
   // what a phi plane of the grown tile holds: 1 phi = +1, 2 phi = -1, 4 a fluid
@@ -824,6 +877,7 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
   float nxt[3];
   load_phi(z0 + 2, nxt);
   if ((t & 63) == 0) wcls[1][t >> 6] = pcls;
+  if (t == 0) lds.n_wet = 0u;
   __syncthreads();
   // four bits for each of the phi planes z + 2 - k (k = 0 .. 4) of the current
   // plane z, once the loop has shifted in plane z + 2
@@ -834,21 +888,24 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
     if (pure_class(lo & 15u))
       zero_normals(z0 - 1, (lo & 8u) != 0u);
     else if (lo & 8u)
-      normals(z0 - 1, with_solids);
+      normals(z0 - 1, 0, with_solids);
     else
-      normals(z0 - 1, no_solids);
+      normals(z0 - 1, 0, no_solids);
     if (pure_class(hi & 15u))
       zero_normals(z0, (hi & 8u) != 0u);
     else if (hi & 8u)
-      normals(z0, with_solids);
+      normals(z0, 1, with_solids);
     else
-      normals(z0, no_solids);
+      normals(z0, 1, no_solids);
   }
   __syncthreads();  // the loop's first phi store reuses the slot of plane z0 - 2
+  if (hist & 0x8888u) rotate_wet(z0 - 1);
   // kept in a register: read from s after the stores below, it would be a
   // load behind them (they may alias s) and its wait would wait for them too
   const float csf = -0.5f * s.sigma;
   const int s_mtx = s.mtiles_x, s_mty = s.mtiles_y;
+  // (not compiled in: instances per storage are slower, 512x256x192 192 -> 204 us
+  // in FP32, 233 -> 247 in FP16)
   const bool fp16 = s.storage != 0;
   GLB uint8_t* __restrict__ KIND = gp(s.kind);
   for (int zz = 0; zz < kz; ++zz) {
@@ -871,9 +928,9 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
     if (pure_class(near & 15u))
       zero_normals(z + 1, (near & 8u) != 0u);
     else if (near & 8u)
-      normals(z + 1, with_solids);
+      normals(z + 1, 0, with_solids);
     else
-      normals(z + 1, no_solids);
+      normals(z + 1, 0, no_solids);
     if (pure) {
       // no normal, curvature or |G|; the solid-neighbour bits where there are
       // solids, from phi.  Without solids nothing of the rings is read here, and the
@@ -911,13 +968,14 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
       continue;
     }
     __syncthreads();
+    if (near & 8u) rotate_wet(z + 1);
     // the curvature reads the normals of planes z - 1 .. z + 1
     const bool csol = (hist & 0x8880u) != 0u;
     if (in && !csol) {
       const int c0 = (lx + 1) + HX * (ly + 1);
       const int n = gx + nx * (gy + ny * z);
       const int s0 = nslot(z);
-      const v4f own = v4f{nrx[s0][c0], nry[s0][c0], nrz[s0][c0], nrg[s0][t]};
+      const v4f own = v4f{nrx[s0][c0], nry[s0][c0], nrz[s0][c0], nrg[gslot(z)][t]};
       float kappa = 0.f;
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
@@ -940,7 +998,7 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
       const int c0 = (lx + 1) + HX * (ly + 1);
       const int n = gx + nx * (gy + ny * z);
       const int s0 = nslot(z);
-      const v4f own = v4f{nrx[s0][c0], nry[s0][c0], nrz[s0][c0], nrg[s0][t]};
+      const v4f own = v4f{nrx[s0][c0], nry[s0][c0], nrz[s0][c0], nrg[gslot(z)][t]};
       float c = 0.f;
       uint32_t bits = 0x80000000u;
       if (own.w >= 0.f) {
@@ -987,17 +1045,20 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
 }
 
 // W64: as for the moments pass
-template <bool OPEN, bool W64>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_interface(Batch bt) {
+template <int GEO, bool W64>
+// six waves per SIMD and blocks per CU; with a textured wall five, as its rotation
+// would spill
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(GEO == GEO_BOXES ? 5 : 6, 8))) void k_interface(Batch bt) {
   __shared__ IfLds lds;
   const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
   const SimDev& s = bt.tab[sb.x];
   if (W64 || s.mtile_lx == 6)
-    interface_block<OPEN, 6>(bt, s, sb, lds);
+    interface_block<GEO, 6>(bt, s, sb, lds);
   else if (s.mtile_lx == 5)
-    interface_block<OPEN, 5>(bt, s, sb, lds);
+    interface_block<GEO, 5>(bt, s, sb, lds);
   else
-    interface_block<OPEN, 4>(bt, s, sb, lds);
+    interface_block<GEO, 4>(bt, s, sb, lds);
 }
 
 // per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
@@ -1519,20 +1580,18 @@ static inline unsigned nblocks(long long n, int b) { return (unsigned)((n + b - 
 // nblk: total 256-node blocks; np_rows: total particle rows; Bmax: the largest
 // mask-box side of the batch.
 // mnblk: blocks of the moments tiling
-hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
-  const dim3 g(mnblk), t(256);
-  if (b.general) {
-    if (b.mlx == 6)
-      hipLaunchKernelGGL((k_interface<true, true>), g, t, 0, st, b);
-    else
-      hipLaunchKernelGGL((k_interface<true, false>), g, t, 0, st, b);
-  } else {
-    if (b.mlx == 6)
-      hipLaunchKernelGGL((k_interface<false, true>), g, t, 0, st, b);
-    else
-      hipLaunchKernelGGL((k_interface<false, false>), g, t, 0, st, b);
-  }
+template <int GEO>
+static hipError_t launch_interface_geo(const Batch& b, unsigned mnblk, hipStream_t st) {
+  if (b.mlx == 6)
+    hipLaunchKernelGGL((k_interface<GEO, true>), dim3(mnblk), dim3(256), 0, st, b);
+  else
+    hipLaunchKernelGGL((k_interface<GEO, false>), dim3(mnblk), dim3(256), 0, st, b);
   return hipGetLastError();
+}
+hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
+  if (b.geometry == GEO_PLAIN) return launch_interface_geo<GEO_PLAIN>(b, mnblk, st);
+  if (b.geometry == GEO_TUBE) return launch_interface_geo<GEO_TUBE>(b, mnblk, st);
+  return launch_interface_geo<GEO_BOXES>(b, mnblk, st);
 }
 
 // cap_rows particle rows (0: none) fill their capillary boxes of at most Bcap nodes
