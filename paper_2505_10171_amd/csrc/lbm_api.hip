@@ -2,7 +2,8 @@
 //
 // The context carves the caller's device workspace, uploads the initial state,
 // and issues the per-step kernel sequence on the caller's stream:
-//   k_fused (collide + recolour + stream + bounce-back + momentum exchange)
+//   k_interface (normal, curvature, kinds of the tile planes)
+//   k_fused (collide + recolour + stream + bounce-back)
 //   k_links (moving walls, momentum exchange, capillary force; its capillary
 //   boxes are filled with k_fused)               -- if the sim has particles
 //   k_dem (contacts, friction, Verlet sub-steps)

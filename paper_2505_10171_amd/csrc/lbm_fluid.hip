@@ -13,7 +13,8 @@
 // coefficient from phi, in one z-march), k_fused (collision, force, streaming and
 // bounce-back of f, one thread per node, reading and writing every population
 // exactly once), k_links (moving-wall terms and momentum exchange at particle
-// links) and k_moments (density and order parameter of the post-stream state).
+// links, and the particles' capillary forces) and k_moments (density and order
+// parameter of the post-stream state).
 #include <algorithm>
 
 #include "lbm_device.h"
