@@ -237,8 +237,8 @@ __global__ __launch_bounds__(64 * (RB / RT) * (8 / CT))
 // hidden layers, and dz of all five layers.  A batch of 256 rows is eight
 // workgroups and waits on the latency of its nine products, each of whose weight
 // fragments are requested one product ahead; layer by layer it was ten launches.
-// A whole batch with its weight pass: 256 rows 38 us (160 before, 24 launches),
-// 64 rows 30, 1,024 rows 92, 4,096 rows 290, about a third each.
+// A whole batch with its weight pass: 256 rows 34 us (160 before, 24 launches),
+// 64 rows 28, 1,024 rows 64, 4,096 rows 144.
 // BIG: the hidden layers' forward products with v_mfma_f32_32x32x16_bf16 (batches
 // of a multiple of 128 rows, as always), else 16x16x32 like all others; the two
 // round their sums differently, so the choice stays with the batch size.
@@ -477,13 +477,22 @@ __device__ __forceinline__ T* pick(T* const* a, int l) {
 // tiles, 16 for each hidden layer and the last layer's four
 constexpr int W_TILES = 4 + 3 * 16 + 4, B_TILES = 4 * 4 + 1;
 constexpr int COLSUM_WAVES = 16;
+constexpr int W_AHEAD = 4;  // K steps of rows in flight
 
-__device__ __forceinline__ float adam(const WeightArgs& g, int i, float gi) {
-  const float mi = 0.9f * g.m[i] + 0.1f * gi;
-  const float vi = 0.999f * g.v[i] + 0.001f * gi * gi;
+// a parameter with its moments, read well before its update: read in turn behind
+// the stores of the one before, each would wait for those (16 round trips of a lane)
+struct AdamState {
+  float p, m, v;
+};
+__device__ __forceinline__ AdamState adam_load(const WeightArgs& g, int i) {
+  return AdamState{g.p[i], g.m[i], g.v[i]};
+}
+__device__ __forceinline__ float adam(const WeightArgs& g, int i, const AdamState& a, float gi) {
+  const float mi = 0.9f * a.m + 0.1f * gi;
+  const float vi = 0.999f * a.v + 0.001f * gi * gi;
   g.m[i] = mi;
   g.v[i] = vi;
-  const float pi = g.p[i] - g.lr * (mi / g.bc1) / (sqrtf(vi / g.bc2) + 1e-8f);
+  const float pi = a.p - g.lr * (mi / g.bc1) / (sqrtf(vi / g.bc2) + 1e-8f);
   g.p[i] = pi;
   return pi;
 }
@@ -497,27 +506,38 @@ __global__ __launch_bounds__(256) void k_train_weights(WeightArgs g) {
   if (blockIdx.x >= W_TILES) {
     // column sums of 64 columns: 16 interleaved groups of 8 rows, added in order
     const int bt = blockIdx.x - W_TILES, l = bt >> 2, n = (bt & 3) * 64 + lane;
-    const int ld = l == 4 ? 64 : 256;
+    const int ld = l == 4 ? 64 : 256, i = b_at(l) + n;
+    AdamState st = {};
+    if (APPLY && w == 0) st = adam_load(g, i);
     const bf16* D = pick(g.dz, l);
-    for (int q = w; q < COLSUM_WAVES; q += 4) {
-      float s = 0.f;
-      for (int m0 = 8 * q; m0 < g.B; m0 += 8 * COLSUM_WAVES) {
-        float v[8];
+    // a wave its four groups together, 32 rows in flight: group after group the
+    // sums were the longest chain of the launch (a batch of 256 rows 38 -> 34 us,
+    // 1,024 rows 92 -> 64, 4,096 rows 290 -> 144)
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < g.B; c0 += 8 * COLSUM_WAVES) {
+      float v[4][8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = m0 + u < g.B ? (float)D[(long long)(m0 + u) * ld + n] : 0.f;
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
-      }
-      part[q][lane] = s;
+        for (int u = 0; u < 8; ++u) {
+          const int m = c0 + 8 * (w + 4 * q) + u;
+          v[q][u] = (float)D[(long long)min(m, g.B - 1) * ld + n];
+          if (m >= g.B) v[q][u] = 0.f;
+        }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum[q] += v[q][u];
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[w + 4 * q][lane] = sum[q];
     __syncthreads();
     if (w == 0) {
       float s = 0.f;
 #pragma unroll
       for (int q = 0; q < COLSUM_WAVES; ++q) s += part[q][lane];
-      const int i = b_at(l) + n;
       if (APPLY)
-        adam(g, i, s);
+        adam(g, i, st, s);
       else
         g.g[i] = s;
     }
@@ -545,18 +565,37 @@ __global__ __launch_bounds__(256) void k_train_weights(WeightArgs g) {
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 va = load_a(0), vd = load_d(0);
+  bf16x8 va[W_AHEAD], vd[W_AHEAD];
+#pragma unroll
+  for (int u = 0; u < W_AHEAD; ++u)
+    if (32 * u < g.B) {
+      va[u] = load_a(32 * u);
+      vd[u] = load_d(32 * u);
+    }
   const int fr = lane & 15, fk = (lane >> 4) * 8;
-  for (int k0 = 0; k0 < g.B; k0 += 32) {
+  // lane holds rows (lane / 16) * 4 + r (r = 0..3) of column lane % 16 per block
+  auto row = [&](int i, int r) { return m0 + wm + i * 16 + (lane >> 4) * 4 + r; };
+  auto col = [&](int j) { return n0 + wn + j * 16 + (lane & 15); };
+  AdamState st[2][2][4];
+  if (APPLY) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          st[i][j][r] = adam_load(g, w_at(l) + min(row(i, r), M - 1) * N + col(j));
+  }
+  auto step = [&](int k0, bf16x8& na, bf16x8& nd) {
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 8; ++j) As[(sc + j) * LD + sk] = va[j];
+    for (int j = 0; j < 8; ++j) As[(sc + j) * LD + sk] = na[j];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) Bs[(sc + j) * LD + sk] = vd[j];
+    for (int j = 0; j < 8; ++j) Bs[(sc + j) * LD + sk] = nd[j];
     __syncthreads();
-    if (k0 + 32 < g.B) {
-      va = load_a(k0 + 32);
-      vd = load_d(k0 + 32);
+    if (k0 + 32 * W_AHEAD < g.B) {
+      na = load_a(k0 + 32 * W_AHEAD);
+      nd = load_d(k0 + 32 * W_AHEAD);
     }
     bf16x8 a[2], b[2];
 #pragma unroll
@@ -568,20 +607,23 @@ __global__ __launch_bounds__(256) void k_train_weights(WeightArgs g) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-  // lane holds rows (lane / 16) * 4 + r (r = 0..3) of column lane % 16 per block
+  };
+  for (int k0 = 0; k0 < g.B; k0 += 32 * W_AHEAD)
+#pragma unroll
+    for (int u = 0; u < W_AHEAD; ++u)
+      if (k0 + 32 * u < g.B) step(k0 + 32 * u, va[u], vd[u]);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn + j * 16 + (lane & 15);
+      const int n = col(j);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int k = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
+        const int k = row(i, r);
         if (k >= M) continue;
         const int e = w_at(l) + k * N + n;
         if (APPLY) {
-          const bf16 x = (bf16)adam(g, e, acc[i][j][r]);
+          const bf16 x = (bf16)adam(g, e, st[i][j][r], acc[i][j][r]);
           g.wf[t_at(l) + wf_index(M, k, n)] = x;
           g.wg[t_at(l) + wg_index(M, k, n)] = x;
           g.wb[t_at(l) + wb_index(N, k, n)] = x;
