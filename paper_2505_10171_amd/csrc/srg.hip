@@ -452,7 +452,7 @@ __global__ __launch_bounds__(512) void k_train_rows(RowArgs g) {
 // and with APPLY the Adam update of what the workgroup owns: the gradient never
 // leaves its registers, and the BF16 copies of the new weights are written in
 // their fragment orders.  The batch is the contraction, in steps of 32 rows
-// through LDS (both operands transposed while staging), the next step's rows in
+// through LDS (both operands transposed while staging), the next four steps' rows in
 // flight.  56 + 17 workgroups on 256 CUs: bound by the latency of the B / 32
 // steps; ten gradient launches, Adam and five transposes before.
 struct WeightArgs {
