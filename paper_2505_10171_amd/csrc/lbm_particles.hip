@@ -916,31 +916,38 @@ __global__ __launch_bounds__(DEM_SMALL * DEM_LANES) void k_dem(Batch bt) {
       }
       const bool active = has && delta > 0.0;
       int slot = has ? (int)me.slot[it] : -1;
-      // new contacts take the free slots in item order (free before this pass)
-      const bool fresh = active && slot < 0;
-      const unsigned need = group(fresh);
-      if (fresh) {
-        unsigned m = ~used & 0xffffu;
-        for (int k = __popc(need & below); k > 0; --k) m &= m - 1u;
-        if (m) {
-          slot = __ffs((int)m) - 1;
-          me.ct[slot].partner = partner;
-          for (int k = 0; k < 3; ++k) me.ct[slot].xt[k] = me.ct[slot].xr[k] = 0.0;
-          me.slot[it] = (int8_t)slot;
-        } else {
-          atomicOr(&s.counters[1], (uint32_t)ST_CONTACT_FULL);
+      const bool ended = has && !active && slot >= 0, fresh = active && slot < 0;
+      if (__any(ended || fresh)) {
+        const unsigned out = group(ended), need = group(fresh);
+        unsigned freed = 0u;
+        for (unsigned m = out; m; m &= m - 1u)
+          freed |= 1u << __shfl(slot, __ffs((int)m) - 1, DEM_LANES);
+        if (ended) {  // its springs are released
+          me.ct[slot].partner = -100;
+          me.slot[it] = -1;
         }
+        // (another lane may take the slot below: not moved past that)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // new contacts take the free slots in item order: as many as there are once
+        // the lower items whose contacts end in this pass have given up theirs
+        unsigned open = (~used | freed) & 0xffffu;
+        if (fresh) {
+          const int rank = __popc(need & below);
+          unsigned m = open;
+          for (int k = rank; k > 0; --k) m &= m - 1u;
+          if (rank < __popc(~used & 0xffffu) + __popc(out & below)) {
+            slot = __ffs((int)m) - 1;
+            me.ct[slot].partner = partner;
+            for (int k = 0; k < 3; ++k) me.ct[slot].xt[k] = me.ct[slot].xr[k] = 0.0;
+            me.slot[it] = (int8_t)slot;
+          } else {
+            atomicOr(&s.counters[1], (uint32_t)ST_CONTACT_FULL);
+          }
+        }
+        for (unsigned m = need; m; m &= m - 1u) open &= open - 1u;
+        used = ~open & 0xffffu;
       }
-      const bool ended = has && !active && slot >= 0;
-      const int freed = slot;
-      if (ended) {  // its springs are released
-        me.ct[slot].partner = -100;
-        me.slot[it] = -1;
-      }
-      for (unsigned m = need; m; m &= m - 1u) used |= used + 1u;
-      used &= 0xffffu;
-      for (unsigned m = group(ended); m; m &= m - 1u)
-        used &= ~(1u << __shfl(freed, __ffs((int)m) - 1, DEM_LANES));
       if (active && slot >= 0) {
         double Fo[3], To[3];
         contact_force(s, &me.ct[slot], delta, nh, vw.vp, vw.wp, vj, wj, Rc, Rcj, arm, mu, mur, dt,
