@@ -17,6 +17,7 @@
 // parameter of the post-stream state).
 #include <algorithm>
 
+#include "launch_rules.h"
 #include "lbm_device.h"
 
 namespace lbm {
@@ -1614,11 +1615,11 @@ hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
 // a side, in a step
 hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows, int Bcap,
                         hipStream_t st) {
-  const int cap_blocks = (int)nblocks((long long)Bcap * Bcap * Bcap, 256);
   const dim3 t(256);
   float* const no = nullptr;
   if (storage == 0) {
-    const dim3 grid(nblk + (unsigned)(cap_rows * cap_blocks));
+    const int cap_blocks = capillary_blocks(nblk, cap_rows, Bcap);
+    const dim3 grid(nblk + (unsigned)cap_rows * (unsigned)cap_blocks);
     if (b.open)
       hipLaunchKernelGGL((k_fused<0, MODE_STEP, true>), grid, t, 0, st, b, cap_rows, cap_blocks, no,
                          no, no, no);
@@ -1627,7 +1628,8 @@ hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows
                          no, no, no, no);
   } else {
     if (cap_rows > 0)
-      hipLaunchKernelGGL(k_capbox, dim3((unsigned)cap_blocks, (unsigned)cap_rows), t, 0, st, b);
+      hipLaunchKernelGGL(k_capbox, dim3((unsigned)capillary_blocks(0, 1, Bcap), (unsigned)cap_rows),
+                         t, 0, st, b);
     if (b.open)
       hipLaunchKernelGGL((k_fused<1, MODE_STEP, true>), dim3(nblk), t, 0, st, b, 0, 0, no, no, no,
                          no);
