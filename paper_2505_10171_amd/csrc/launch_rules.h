@@ -17,4 +17,12 @@ inline int capillary_blocks(long long fluid_blocks, long long rows, int side) {
   return (int)std::max(1ll, std::min((nodes + 255) / 256, room));
 }
 
+// Whether a kernel may store an output at the caller's pointer: device memory of the
+// GPU that holds the workspace (own; -1 if unknown).  Anything else that a copy
+// reaches, another GPU's memory above all, which a kernel may not have access to, is
+// written by a copy.
+inline bool stores_directly(bool device_memory, int device, int own) {
+  return device_memory && own >= 0 && device == own;
+}
+
 }  // namespace lbm

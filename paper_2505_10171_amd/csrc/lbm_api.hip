@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "../../include/lbm.h"
+#include "launch_rules.h"
 #include "lbm_device.h"
 
 namespace lbm {
@@ -305,6 +306,7 @@ struct lbm_ctx {
   std::vector<SimHost> sims;
   hipStream_t stream;
   int dev = 0;  // device current at creation
+  int ws_dev = -1;  // device that holds the workspace
   char* ws;
   size_t ws_bytes;
   int err;
@@ -487,6 +489,17 @@ static int set_err(lbm_ctx* c, int code, const char* fmt, ...) {
     if (e_ != hipSuccess)                                                                  \
       return set_err((ctx), LBM_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));      \
   } while (0)
+
+// the GPU whose memory p points to, -1 for anything else
+static int device_of(const void* p) {
+  hipPointerAttribute_t a;
+  memset(&a, 0, sizeof a);
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  return a.type == hipMemoryTypeDevice ? a.device : -1;
+}
 
 // Device batch tables (simulation records, block prefix of the per-node
 // kernels, particle rows) and their extents; at creation `off` is the end of the
@@ -741,6 +754,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
       if (hipStreamSynchronize(st) != hipSuccess) return fail(LBM_EHIP, "synchronise failed");
     }
   }
+  ctx->ws_dev = device_of(ctx->ws);
   default_marches(ctx->sims);
   // batch tables: simulation records, block prefix, particle rows
   ctx->storage = cfg[0].storage;
@@ -1186,12 +1200,13 @@ int lbm_fields2(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, 
   const long long N = d.N;
   const hipMemcpyKind kind = dst_is_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
   if (what & (LBM_F_RHO | LBM_F_U | LBM_F_PHI | LBM_F_FORCE)) {
-    // written straight to device buffers; for host buffers through the spare
-    // population buffer: rho | phi | u | F (8N floats)
+    // written straight to buffers of the workspace's own GPU; to others through the
+    // spare population buffer: rho | phi | u | F (8N floats)
     float* scratch = (float*)d.pops[ctx->cur ^ 1];
     auto out = [&](uint32_t bit, float* dst, long long off) -> float* {
       if (!(what & bit) || !dst) return nullptr;
-      return dst_is_device ? dst : scratch + off;
+      const int dev = dst_is_device ? device_of(dst) : -1;
+      return stores_directly(dev >= 0, dev, ctx->ws_dev) ? dst : scratch + off;
     };
     float* orho = out(LBM_F_RHO, rho, 0);
     float* ophi = out(LBM_F_PHI, phi, N);
@@ -1200,12 +1215,10 @@ int lbm_fields2(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, 
     const Batch b1 = batch_one(ctx, sim);
     HIPCHK(ctx, launch_interface(b1, mom_blocks(d, b1.mkz), ctx->stream));
     HIPCHK(ctx, launch_fields(b1, ctx->storage, sim_blocks(d), orho, ou, ophi, oF, ctx->stream));
-    if (!dst_is_device) {
-      if (oF) HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));
-      if (orho) HIPCHK(ctx, hipMemcpyAsync(rho, orho, 4 * N, kind, ctx->stream));
-      if (ophi) HIPCHK(ctx, hipMemcpyAsync(phi, ophi, 4 * N, kind, ctx->stream));
-      if (ou) HIPCHK(ctx, hipMemcpyAsync(u, ou, 12 * N, kind, ctx->stream));
-    }
+    if (oF && oF != force) HIPCHK(ctx, hipMemcpyAsync(force, oF, 12 * N, kind, ctx->stream));
+    if (orho && orho != rho) HIPCHK(ctx, hipMemcpyAsync(rho, orho, 4 * N, kind, ctx->stream));
+    if (ophi && ophi != phi) HIPCHK(ctx, hipMemcpyAsync(phi, ophi, 4 * N, kind, ctx->stream));
+    if (ou && ou != u) HIPCHK(ctx, hipMemcpyAsync(u, ou, 12 * N, kind, ctx->stream));
   }
   if ((what & LBM_F_MASK) && mask)
     HIPCHK(ctx, hipMemcpyAsync(mask, d.mask, 2 * N, kind, ctx->stream));

@@ -37,3 +37,12 @@ def test_capillary_blocks_fit_the_grid(rule, nodes, rows, R):
     assert 1 <= per <= full and fluid + rows * per <= GRID_BLOCKS
     # a node per thread wherever that fits
     assert per == full or fluid + rows * (per + 1) > GRID_BLOCKS
+
+
+def test_where_a_kernel_stores_directly(rule):
+    """Only into memory of the workspace's own GPU; -1: not device memory, or unknown."""
+    got = rule("stores_directly(true, 0, 0)", "stores_directly(true, 1, 1)",
+               "stores_directly(true, 1, 0)", "stores_directly(true, 0, 1)",
+               "stores_directly(false, -1, 0)", "stores_directly(false, -1, -1)",
+               "stores_directly(false, 0, 0)", "stores_directly(true, 0, -1)")
+    assert got == [1, 1, 0, 0, 0, 0, 0, 0]
