@@ -195,7 +195,9 @@ int lbm_sync(lbm_ctx* ctx);
  * capillary-force eq. and the DEM's net contact force.  dir 1 (PUSH): replace
  * the particle state (x, v, w, q and properties) from parts (a prescribed
  * path, as the detachment benchmark's); contact springs are kept; the mask is
- * rebuilt and fresh fluid nodes are refilled (refilling eqs.).  Synchronous. */
+ * rebuilt and fresh fluid nodes are refilled (refilling eqs.).  A simulation
+ * whose steps have failed keeps its particles: the failure is reported, before
+ * anything that is wrong with the records.  Synchronous. */
 int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* parts, int32_t n,
                        double* history, int32_t max_steps, int32_t* n_hist);
 

@@ -1069,14 +1069,15 @@ int lbm_profile_read(lbm_ctx* ctx, double* total_ms, int64_t* launches, int32_t 
 // Device status words of every simulation (only = one simulation's), in one
 // copy (an ensemble of 64 read by itself, one simulation at a time, had spent
 // 64 copies and waits on each); waits for the stream
-static int check_status(lbm_ctx* ctx, int only = -1) {
+// (lead: the one whose status comes first)
+static int check_status(lbm_ctx* ctx, int only = -1, int lead = 0) {
   const int first = only >= 0 ? only : 0, n = only >= 0 ? 1 : (int)ctx->sims.size();
   std::vector<uint32_t> words((size_t)COUNTERS * n);
   HIPCHK(ctx, hipMemcpyAsync(words.data(), ctx->d_counters + (size_t)COUNTERS * first,
                              4 * words.size(), hipMemcpyDeviceToHost, ctx->stream));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  for (int k = 0; k < n; ++k) {
-    const uint32_t* cnt = &words[(size_t)COUNTERS * k];
+  for (int k = -1; k < n; ++k) {
+    const uint32_t* cnt = &words[(size_t)COUNTERS * (k >= 0 ? k : only >= 0 ? 0 : lead)];
     if (cnt[1] & ST_UNSTABLE)
       return set_err(ctx, LBM_EUNSTABLE, "unstable flow: NaN, rho <= 0 or |u| > 0.3");
     if (cnt[1] & ST_CONTACT_FULL)
@@ -1107,11 +1108,13 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
   if (!sh) return set_err(ctx, LBM_ERANGE, "simulation index out of range");
   SimDev& d = sh->d;
   if (n != d.np || (n > 0 && !parts)) return set_err(ctx, LBM_EINVAL, "particle count mismatch");
-  // (a push reports the status when it is done)
-  int rc = dir == 0 ? check_status(ctx, sim) : LBM_OK;
+  // A failed simulation is reported first, its particles left alone.  A push finds out
+  // on the device (k_push), without a wait of its own, and reports at its end; records
+  // that it refuses come after the status all the same.
+  int rc = dir != 1 || d.np == 0 ? check_status(ctx, sim) : LBM_OK;
   if (rc) return rc;
   if (n_hist) *n_hist = 0;
-  if (d.np == 0) return check_status(ctx, sim);
+  if (d.np == 0) return LBM_OK;
   if (dir == 0) {
     std::vector<DevParticle> hp(d.np);
     HIPCHK(ctx, hipMemcpyAsync(hp.data(), d.P, sizeof(DevParticle) * d.np, hipMemcpyDeviceToHost,
@@ -1164,9 +1167,11 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
   if (dir != 1) return set_err(ctx, LBM_EINVAL, "dir must be 0 (pull) or 1 (push)");
   char msg[256];
   for (int p = 0; p < d.np; ++p) {
-    if (!valid_particle(sh->cfg, parts[p], msg, sizeof msg)) return set_err(ctx, LBM_EINVAL, "%s", msg);
-    if (parts[p].R > sh->Rmax)
-      return set_err(ctx, LBM_ERANGE, "radius exceeds the largest radius the context was sized for");
+    const bool valid = valid_particle(sh->cfg, parts[p], msg, sizeof msg);
+    if (valid && !(parts[p].R > sh->Rmax)) continue;
+    if ((rc = check_status(ctx, sim))) return rc;
+    if (!valid) return set_err(ctx, LBM_EINVAL, "%s", msg);
+    return set_err(ctx, LBM_ERANGE, "radius exceeds the largest radius the context was sized for");
   }
   // the state and properties lead the record; they are staged where the DEM keeps
   // its views, which no step reads before it writes them
@@ -1182,7 +1187,7 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
   HIPCHK(ctx, launch_push(d, ctx->stream));
   rc = post_dem_pipeline(ctx, sim, true);
   if (rc) return rc;
-  return lbm_sync(ctx);
+  return check_status(ctx, -1, sim);
 }
 
 int lbm_fields(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, float* phi,

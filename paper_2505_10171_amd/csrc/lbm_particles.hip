@@ -42,11 +42,13 @@ __device__ __attribute__((noinline)) bool inside_sphere(int x, int y, int z, con
 }
 
 // Pushed particles: the heads of their records, staged in the view buffer,
-// into the records, whose present centre and radius the mask update releases.
+// into the records, whose present centre and radius the mask update releases.  A
+// simulation that has failed (status flags) keeps its records; the mask update then
+// finds every node as it is.
 static_assert(2 * sizeof(DemView) >= sizeof(DevParticleHead), "the views hold the heads");
 __global__ void k_push(SimDev s) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= s.np) return;
+  if (p >= s.np || s.counters[1] != 0u) return;
   DevParticle& P = s.P[p];
   const DevParticleHead h = ((const DevParticleHead*)s.view)[p];
   for (int d = 0; d < 3; ++d) P.xo[d] = P.x[d];
