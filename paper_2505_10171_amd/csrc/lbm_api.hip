@@ -7,7 +7,8 @@
 //   k_links (moving walls, momentum exchange, capillary force; its capillary
 //   boxes are filled with k_fused)               -- if the sim has particles
 //   k_dem (contacts, friction, Verlet sub-steps)
-//   k_mask (solid mask of the new positions)
+//   k_mask (solid mask of the new positions; with many particles k_claim, k_release
+//   and k_cover)
 //   k_moments (fresh fluid nodes refilled, order parameter of the new state)
 // No device memory is allocated and nothing is synchronised inside lbm_step.
 #include <math.h>
@@ -43,7 +44,7 @@ hipError_t launch_init_pops(const SimDev& s, void* pops, hipStream_t st);
 hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, double* acc,
                        hipStream_t st);
 hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
-hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
+hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, bool with_release,
                               hipStream_t st);
 hipError_t launch_push(const SimDev& s, hipStream_t st);
 hipError_t launch_dem(const Batch& b, int np_max, int np_rows, int n_sub_max, hipStream_t st);
@@ -90,7 +91,7 @@ struct SimLayout {
   long long N;
   int np, Bmask, Bcap, hist_cap;
   size_t pop_bytes, fresh_cap;
-  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_fresh, off_fresh_own,
+  size_t off_pops0, off_pops1, off_rp0, off_rp1, off_nrm, off_cur, off_kind, off_mask, off_claim, off_fresh, off_fresh_own,
       off_P, off_ct, off_nb, off_view, off_hist, off_capbox, off_mass,
       off_step;
   size_t total;
@@ -203,7 +204,7 @@ SimLayout layout(const lbm_config& c, double Rmax, int hist_cap, size_t base) {
     L.off_kind = take((size_t)t.mtiles_x * t.mtiles_y * t.nz);
   }
   L.off_mask = take(2 * L.N);
-  (void)take(4 * L.N);  // unused: callers rely on 46 bytes per node besides the populations
+  L.off_claim = take(4 * L.N);
   L.off_fresh = take(4 * L.fresh_cap);
   L.off_fresh_own = take(4 * L.fresh_cap);
   L.off_P = take(sizeof(DevParticle) * L.np);
@@ -571,7 +572,7 @@ static int post_dem_pipeline(lbm_ctx* ctx, int si, bool with_release) {
   Batch b = batch_one(ctx, si);
   b.fc = 2;
   if (s.np > 0)
-    HIPCHK(ctx, launch_mask_update(b, s.np, sh.L.Bmask, with_release, ctx->stream));
+    HIPCHK(ctx, launch_mask_update(b, s.np, s.np, sh.L.Bmask, with_release, ctx->stream));
   HIPCHK(ctx, launch_boundary(b, ctx->storage, sim_blocks(s), s.fresh_cap, s.np, ctx->stream));
   return LBM_OK;
 }
@@ -687,6 +688,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     d.curv = (float2*)(b + sh.L.off_cur);
     d.kind = (uint8_t*)(b + sh.L.off_kind);
     d.mask = (uint16_t*)(b + sh.L.off_mask);
+    d.claim = (uint32_t*)(b + sh.L.off_claim);
     d.fresh = (uint32_t*)(b + sh.L.off_fresh);
     d.fresh_own = (uint32_t*)(b + sh.L.off_fresh_own);
     d.fresh_cap = (uint32_t)sh.L.fresh_cap;
@@ -768,7 +770,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     const Batch b1 = batch_one(ctx, si);
     hipStream_t st = ctx->stream;
     if (launch_init_mask(d, st) != hipSuccess) return fail(LBM_EHIP, "mask init failed");
-    if (d.np > 0 && launch_mask_update(b1, d.np, sh.L.Bmask, false, st) != hipSuccess)
+    if (d.np > 0 && launch_mask_update(b1, d.np, d.np, sh.L.Bmask, false, st) != hipSuccess)
       return fail(LBM_EHIP, "mask build failed");
     if (launch_init_pops(d, d.pops[0], st) != hipSuccess)
       return fail(LBM_EHIP, "population init failed");
@@ -815,7 +817,7 @@ static int step_once(lbm_ctx* ctx, int slot) {
   const Batch a = batch_all(ctx);
   if (ctx->np_rows > 0) {
     HIPCHK(ctx, launch_dem(a, ctx->np_max, ctx->np_rows, ctx->n_sub_max, st));
-    HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->Bmax, true, st));
+    HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->np_max, ctx->Bmax, true, st));
   }
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][4], st));
   HIPCHK(ctx, launch_moments(a, ctx->storage, ctx->mnblk, ctx->fresh_cap_max, ctx->np_max, st));

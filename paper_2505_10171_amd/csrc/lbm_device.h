@@ -198,6 +198,7 @@ struct SimDev {
   // (z mtiles_y + tile y) mtiles_x + tile x), a TileKind of the colliding state
   uint8_t* kind;
   uint16_t* mask;      // 0 fluid, 1 wall, 2+p particle p; FRESH_BIT while refilling
+  uint32_t* claim;     // per node: lowest particle claiming it in the new mask, ~0u none
   uint32_t* fresh;     // fresh-node list: node index
   uint32_t* fresh_own; // fresh-node list: particle that uncovered it
   uint32_t* counters;  // [0] fresh count of a step, [1] status flags, [2] fresh count between steps

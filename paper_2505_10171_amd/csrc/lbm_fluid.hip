@@ -508,6 +508,7 @@ __global__ void k_init_mask(SimDev s) {
   int z = (int)(n / ((long long)s.nx * s.ny));
   const int x = (int)(n % s.nx), y = (int)((n / s.nx) % s.ny);
   s.mask[n] = static_wall(s, x, y, z) ? 1 : 0;
+  s.claim[n] = 0xFFFFFFFFu;
 }
 
 // fluid at rest: f = w rho0 (d = 0), moments (rho0, phi0) in both moment

@@ -2,6 +2,7 @@
 // capillary force on the Lagrangian surface grid and the DEM (contacts with sliding and rolling friction, velocity Verlet).
 #include <algorithm>
 
+#include "launch_rules.h"
 #include "lbm_device.h"
 
 namespace lbm {
@@ -64,10 +65,15 @@ __global__ void k_push(SimDev s) {
 // owner's; what another block may read there meanwhile (the new code, or the
 // fresh mark) leaves that block's part unchanged, so the pass needs no claims in
 // memory and no second and third kernel (one launch for three: 12 -> 5 us
-// with one sphere of radius 4, 14 -> 6.6 with 20 of radius 5, 39 -> 33 with 500
-// of radius 4, whose blocks each look through all of them).
+// with one sphere of radius 4, 14 -> 6.6 with 20 of radius 5, 40 -> 34 with 500
+// of radius 4).  But each block looks through all particles, so that boxes of many
+// take the claims below; and the grid is sized by the largest sphere, so it is bounded
+// (particle_blocks) and a block past both boxes of its own leaves before that (one
+// sphere of radius 20 beside 400 of radius 3: 437 us without, 60 with).
 constexpr int MASK_NEAR = 64;  // overlapping particles listed; more: all are tested
-template <bool RELEASE>
+// STRIDE: the grid is bounded, the blocks take several turns (that loop takes 24 VGPRs
+// and three waves per SIMD more: 97 -> 106 us with 500 spheres of radius 8)
+template <bool RELEASE, bool STRIDE>
 __global__ __launch_bounds__(256) void k_mask(Batch bt) {
   const int2 sp = batch_particle(bt, blockIdx.y);
   const SimDev& s = bt.tab[sp.x];
@@ -78,22 +84,34 @@ __global__ __launch_bounds__(256) void k_mask(Batch bt) {
   const double X[3] = {PP[p].x[0], PP[p].x[1], PP[p].x[2]}, R = PP[p].R;
   const double Xo[3] = {PP[p].xo[0], PP[p].xo[1], PP[p].xo[2]}, Ro = PP[p].Ro;
   GLB uint16_t* __restrict__ MASK = gp(s.mask);
-  // a node's mask code, of both boxes, with the candidates' positions in flight
+  // this block's nodes of both boxes, 256 of each at a time
   const Box b = particle_box(s, X, R), bo = particle_box(s, Xo, Ro);
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  auto vol = [](const Box& q) { return q.w[0] * q.w[1] * q.w[2]; };
+  const int nodes = max(vol(b), RELEASE ? vol(bo) : 0);
+  int k0 = (int)(blockIdx.x * blockDim.x);
+  if (k0 >= nodes) return;
   auto node = [&](const Box& q, int& x, int& y, int& z) -> bool {
-    if (k >= q.w[0] * q.w[1] * q.w[2]) return false;
+    const int k = k0 + (int)threadIdx.x;
+    if (k >= vol(q)) return false;
     x = wrapi(q.lo[0] + k % q.w[0], nx);
     y = wrapi(q.lo[1] + (k / q.w[0]) % q.w[1], ny);
     z = wrapi(q.lo[2] + k / (q.w[0] * q.w[1]), nz);
     return true;
   };
-  int x, y, z, xo = 0, yo = 0, zo = 0;
-  const bool in = node(b, x, y, z), ino = RELEASE && node(bo, xo, yo, zo);
-  const unsigned n = in ? (unsigned)(x + nx * (y + ny * z)) : 0u;
-  const unsigned no = ino ? (unsigned)(xo + nx * (yo + ny * zo)) : 0u;
-  const uint16_t m = at((const GLB uint16_t*)MASK, n);
-  const uint16_t mo = RELEASE ? at((const GLB uint16_t*)MASK, no) : (uint16_t)0;
+  int x = 0, y = 0, z = 0, xo = 0, yo = 0, zo = 0;
+  unsigned n = 0, no = 0;
+  bool in = false, ino = false;
+  uint16_t m = 0, mo = 0;
+  // their mask codes: the first with the candidates' positions in flight
+  auto load = [&]() {
+    in = node(b, x, y, z);
+    ino = RELEASE && node(bo, xo, yo, zo);
+    n = in ? (unsigned)(x + nx * (y + ny * z)) : 0u;
+    no = ino ? (unsigned)(xo + nx * (yo + ny * zo)) : 0u;
+    m = at((const GLB uint16_t*)MASK, n);
+    if (RELEASE) mo = at((const GLB uint16_t*)MASK, no);
+  };
+  load();
   // particles whose new sphere meets p's new or old one: a node inside both
   // spheres is nearer than both radii to both centres (the margin covers rounding)
   __shared__ int near[MASK_NEAR], n_near;
@@ -128,32 +146,129 @@ __global__ __launch_bounds__(256) void k_mask(Batch bt) {
     }
     return c;
   };
-  if (RELEASE) {
-    const bool mine = ino && mo == (uint16_t)(2 + p);
-    const int c = mine ? owner(xo, yo, zo) : p;
-    const bool fresh = c == np;
+  for (;;) {
+    if (RELEASE) {
+      const bool mine = ino && mo == (uint16_t)(2 + p);
+      const int c = mine ? owner(xo, yo, zo) : p;
+      const bool fresh = c == np;
+      // the wave's fresh nodes take consecutive slots of the fresh list: one
+      // atomic per wave (the list's order does not matter to the refill)
+      const unsigned long long want = __ballot(fresh);
+      if (want) {
+        const int lane = (int)(threadIdx.x & 63), first = __ffsll((long long)want) - 1;
+        uint32_t base0 = 0;
+        if (lane == first) base0 = atomicAdd(&s.counters[bt.fc], (uint32_t)__popcll(want));
+        base0 = (uint32_t)__shfl((int)base0, first, 64);
+        if (fresh) {
+          MASK[no] = FRESH_BIT;
+          const uint32_t slot = base0 + (uint32_t)__popcll(want & ((1ull << lane) - 1ull));
+          if (slot < s.fresh_cap) {
+            s.fresh[slot] = no;
+            s.fresh_own[slot] = (uint32_t)p;
+          } else {
+            atomicOr(&s.counters[1], (uint32_t)ST_FRESH_FULL);
+          }
+        }
+      }
+      if (mine && !fresh && c != p) MASK[no] = (uint16_t)(2 + c);
+    }
+    if (in && m == 0 && owner(x, y, z) == p) MASK[n] = (uint16_t)(2 + p);
+    k0 += (int)(gridDim.x * blockDim.x);
+    if (!STRIDE || k0 >= nodes) return;
+    load();
+  }
+}
+
+// The same by claims in memory, three kernels whose time does not grow with the number
+// of particles per block: for boxes of many (mask_by_search).
+// claim: lowest particle index inside which a node lies (new positions)
+__global__ void k_claim(Batch bt) {
+  const int2 sp = batch_particle(bt, blockIdx.y);
+  const SimDev& s = bt.tab[sp.x];
+  const int p = sp.y;
+  const DevParticle& P = s.P[p];
+  const Box b = particle_box(s, P.x, P.R);
+  const int vol = b.w[0] * b.w[1] * b.w[2];
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
+    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
+    const int x = wrapi(b.lo[0] + ix, s.nx), y = wrapi(b.lo[1] + iy, s.ny),
+              z = wrapi(b.lo[2] + iz, s.nz);
+    if (static_wall(s, x, y, z)) continue;
+    if (inside_sphere(x, y, z, P.x, P.R, s.nx, s.ny, s.nz)) {
+      const long long n = (long long)x + (long long)s.nx * ((long long)y + (long long)s.ny * z);
+      atomicMin(&s.claim[n], (uint32_t)p);
+    }
+  }
+}
+
+// release: nodes that belonged to p (old box) become fluid (fresh) or pass to
+// the particle that claims them now.  Each such node is visited once (by p).
+__global__ void k_release(Batch bt) {
+  const int2 sp = batch_particle(bt, blockIdx.y);
+  const SimDev& s = bt.tab[sp.x];
+  const int p = sp.y;
+  const DevParticle& P = s.P[p];
+  double Xo[3] = {P.xo[0], P.xo[1], P.xo[2]};
+  const Box b = particle_box(s, Xo, P.Ro);
+  const int vol = b.w[0] * b.w[1] * b.w[2];
+  // the record's fields held in registers (the stores below may alias it)
+  const int nx = s.nx, ny = s.ny, nz = s.nz;
+  GLB uint16_t* __restrict__ MASK = gp(s.mask);
+  const GLB uint32_t* __restrict__ CLAIM = gp((const uint32_t*)s.claim);
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
+    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
+    const int x = wrapi(b.lo[0] + ix, nx), y = wrapi(b.lo[1] + iy, ny), z = wrapi(b.lo[2] + iz, nz);
+    const unsigned n = (unsigned)(x + nx * (y + ny * z));
+    // mask and claim in one round trip
+    const uint16_t m = at((const GLB uint16_t*)MASK, n);
+    const uint32_t c = at(CLAIM, n);
+    const bool mine = m == (uint16_t)(2 + p);
+    const bool fresh = mine && c == 0xFFFFFFFFu;
     // the wave's fresh nodes take consecutive slots of the fresh list: one
     // atomic per wave (the list's order does not matter to the refill)
     const unsigned long long want = __ballot(fresh);
-    if (want) {
-      const int lane = (int)(threadIdx.x & 63), first = __ffsll((long long)want) - 1;
-      uint32_t base0 = 0;
-      if (lane == first) base0 = atomicAdd(&s.counters[bt.fc], (uint32_t)__popcll(want));
-      base0 = (uint32_t)__shfl((int)base0, first, 64);
-      if (fresh) {
-        MASK[no] = FRESH_BIT;
-        const uint32_t slot = base0 + (uint32_t)__popcll(want & ((1ull << lane) - 1ull));
-        if (slot < s.fresh_cap) {
-          s.fresh[slot] = no;
-          s.fresh_own[slot] = (uint32_t)p;
-        } else {
-          atomicOr(&s.counters[1], (uint32_t)ST_FRESH_FULL);
-        }
+    uint32_t base0 = 0;
+    const int lane = (int)(threadIdx.x & 63);
+    const int first = want ? __ffsll((long long)want) - 1 : 0;
+    if (want && lane == first) base0 = atomicAdd(&s.counters[bt.fc], (uint32_t)__popcll(want));
+    base0 = (uint32_t)__shfl((int)base0, first, 64);
+    if (!mine) continue;
+    if (fresh) {
+      MASK[n] = FRESH_BIT;
+      const uint32_t slot = base0 + (uint32_t)__popcll(want & ((1ull << lane) - 1ull));
+      if (slot < s.fresh_cap) {
+        s.fresh[slot] = n;
+        s.fresh_own[slot] = (uint32_t)p;
+      } else {
+        atomicOr(&s.counters[1], (uint32_t)ST_FRESH_FULL);
       }
+    } else if (c != (uint32_t)p) {
+      MASK[n] = (uint16_t)(2 + c);
     }
-    if (mine && !fresh && c != p) MASK[no] = (uint16_t)(2 + c);
   }
-  if (in && m == 0 && owner(x, y, z) == p) MASK[n] = (uint16_t)(2 + p);
+}
+
+// cover: nodes claimed by p become p's solid nodes; claims are cleared
+__global__ void k_cover(Batch bt) {
+  const int2 sp = batch_particle(bt, blockIdx.y);
+  const SimDev& s = bt.tab[sp.x];
+  const int p = sp.y;
+  const DevParticle& P = s.P[p];
+  const Box b = particle_box(s, P.x, P.R);
+  const int vol = b.w[0] * b.w[1] * b.w[2];
+  // the record's fields held in registers (the stores below may alias it)
+  const int nx = s.nx, ny = s.ny, nz = s.nz;
+  GLB uint16_t* __restrict__ MASK = gp(s.mask);
+  GLB uint32_t* __restrict__ CLAIM = gp(s.claim);
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < vol; k += gridDim.x * blockDim.x) {
+    const int ix = k % b.w[0], iy = (k / b.w[0]) % b.w[1], iz = k / (b.w[0] * b.w[1]);
+    const int x = wrapi(b.lo[0] + ix, nx), y = wrapi(b.lo[1] + iy, ny), z = wrapi(b.lo[2] + iz, nz);
+    const unsigned n = (unsigned)(x + nx * (y + ny * z));
+    if (at((const GLB uint32_t*)CLAIM, n) == (uint32_t)p) {
+      MASK[n] = (uint16_t)(2 + p);
+      CLAIM[n] = 0xFFFFFFFFu;
+    }
+  }
 }
 
 // -------------------------------------------------------------------- DEM
@@ -1016,24 +1131,27 @@ __global__ __launch_bounds__(DEM_SMALL * DEM_LANES) void k_dem(Batch bt) {
 }
 
 // ------------------------------------------------------------ host launchers
-static inline unsigned box_blocks(int B) {
-  const int v = B * B * B;
-  return (unsigned)((v + 255) / 256);
-}
 
 hipError_t launch_push(const SimDev& s, hipStream_t st) {
   hipLaunchKernelGGL(k_push, dim3((unsigned)((s.np + 63) / 64)), dim3(64), 0, st, s);
   return hipGetLastError();
 }
 
-hipError_t launch_mask_update(const Batch& b, int np_rows, int Bmax, bool with_release,
+// np_max: the most particles of one simulation of the batch
+hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, bool with_release,
                               hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
-  dim3 grid(box_blocks(Bmax), np_rows);
-  if (with_release)
-    hipLaunchKernelGGL(k_mask<true>, grid, dim3(256), 0, st, b);
-  else
-    hipLaunchKernelGGL(k_mask<false>, grid, dim3(256), 0, st, b);
+  dim3 grid(particle_blocks(np_rows, Bmax), np_rows);
+  if (!mask_by_search(np_max)) {
+    hipLaunchKernelGGL(k_claim, grid, dim3(256), 0, st, b);
+    if (with_release) hipLaunchKernelGGL(k_release, grid, dim3(256), 0, st, b);
+    hipLaunchKernelGGL(k_cover, grid, dim3(256), 0, st, b);
+    return hipGetLastError();
+  }
+  const bool stride = (long long)grid.x * 256 < (long long)Bmax * Bmax * Bmax;
+  auto* k = with_release ? (stride ? k_mask<true, true> : k_mask<true, false>)
+                         : (stride ? k_mask<false, true> : k_mask<false, false>);
+  hipLaunchKernelGGL(k, grid, dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

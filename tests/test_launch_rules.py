@@ -46,3 +46,13 @@ def test_where_a_kernel_stores_directly(rule):
                "stores_directly(false, -1, 0)", "stores_directly(false, -1, -1)",
                "stores_directly(false, 0, 0)", "stores_directly(true, 0, -1)")
     assert got == [1, 1, 0, 0, 0, 0, 0, 0]
+
+
+@pytest.mark.parametrize("rows,R", [(1, 4), (500, 4), (1, 100), (401, 20), (4096, 10), (60000, 3)])
+def test_particle_blocks(rule, rows, R):
+    side = 2 * R + 4
+    per, = rule(f"particle_blocks({rows}, {side})")
+    full = -(-side ** 3 // 256)
+    assert 1 <= per <= full
+    assert per == 1 or rows * per <= 32768
+    assert per == full or rows * (per + 1) > 32768
