@@ -4,19 +4,6 @@
 
 namespace lbm {
 
-// blocks of 256 threads that one dimension of a grid takes (2^32 - 1 threads)
-constexpr long long GRID_BLOCKS = 0xFFFFFFFFll / 256;
-
-// Blocks per particle that fill its capillary box (`side` nodes a side) when those of
-// `rows` particles share a flat grid with `fluid_blocks` others: a node per thread, or
-// what the grid has room for (the blocks stride over the box): 501 particles of which
-// one has R = 102 would take 17.4 M blocks of the 16.8 M.
-inline int capillary_blocks(long long fluid_blocks, long long rows, int side) {
-  const long long nodes = (long long)side * side * side;
-  const long long room = (GRID_BLOCKS - fluid_blocks) / std::max(1ll, rows);
-  return (int)std::max(1ll, std::min((nodes + 255) / 256, room));
-}
-
 // Whether a kernel may store an output at the caller's pointer: device memory of the
 // GPU that holds the workspace (own; -1 if unknown).  Anything else that a copy
 // reaches, another GPU's memory above all, which a kernel may not have access to, is
@@ -25,16 +12,27 @@ inline bool stores_directly(bool device_memory, int device, int own) {
   return device_memory && own >= 0 && device == own;
 }
 
-// Blocks of 256 per particle of a launch whose grid rows are `rows` particles and whose
-// boxes have at most `side` nodes a side: a node per thread, but no more than PARTICLE_BLOCKS
-// in all (128 per CU); the blocks stride over a box that is larger.  The largest sphere
-// of the context sizes the rows of all, and a block that finds nothing to do takes
-// 0.4 to 1.3 ns of the launch all the same.
-constexpr int PARTICLE_BLOCKS = 32768;
-inline int particle_blocks(long long rows, int side) {
-  const long long nodes = (long long)side * side * side;
-  const long long most = std::max(1ll, PARTICLE_BLOCKS / std::max(1ll, rows));
-  return (int)std::max(1ll, std::min((nodes + 255) / 256, most));
+// blocks of 256 threads for a box of `side` nodes a side, a node per thread
+inline long long box_blocks(double side) { return ((long long)(side * side * side) + 255) / 256; }
+
+// Blocks per particle of a launch whose grid rows are `rows` particles, all with as many
+// as the largest box takes (`side`); `own`: what their own boxes would take together.
+// Where the boxes are much alike, a node per thread.  Else most blocks would find nothing to
+// do, which takes 0.4 to 1.3 ns of the launch each: PARTICLE_BLOCKS in all (128 per CU),
+// and the blocks stride over a box that is larger.
+constexpr long long PARTICLE_BLOCKS = 32768;
+inline int particle_blocks(long long rows, int side, long long own) {
+  const long long full = box_blocks(side), r = std::max(1ll, rows);
+  if (r * full <= std::max(4 * own, PARTICLE_BLOCKS)) return (int)full;
+  return (int)std::max(1ll, std::min(full, PARTICLE_BLOCKS / r));
+}
+
+// The same where they share a flat grid with `fluid_blocks` others: a grid dimension takes
+// 2^32 - 1 threads and is cut short beyond, without an error.
+constexpr long long GRID_BLOCKS = 0xFFFFFFFFll / 256;
+inline int particle_blocks_flat(long long fluid_blocks, long long rows, int side, long long own) {
+  const long long room = (GRID_BLOCKS - fluid_blocks) / std::max(1ll, rows);
+  return (int)std::max(1ll, std::min((long long)particle_blocks(rows, side, own), room));
 }
 
 // Whether the mask update searches the particles in each block (k_mask, one launch) or

@@ -30,7 +30,7 @@
 namespace lbm {
 hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st);
 hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows, int Bcap,
-                        hipStream_t st);
+                        long long own, hipStream_t st);
 hipError_t launch_fields(const Batch& b, int storage, unsigned nblk, float* orho, float* ou,
                          float* ophi, float* oF, hipStream_t st);
 hipError_t launch_links(const Batch& b, int storage, int np_rows, int Bmax, int npts,
@@ -44,8 +44,8 @@ hipError_t launch_init_pops(const SimDev& s, void* pops, hipStream_t st);
 hipError_t launch_mass(const SimDev& s, const float* rp, const void* pops, double* acc,
                        hipStream_t st);
 hipError_t launch_zero_f64(double* p, int n, hipStream_t st);
-hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, bool with_release,
-                              hipStream_t st);
+hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, long long own,
+                              bool with_release, hipStream_t st);
 hipError_t launch_push(const SimDev& s, hipStream_t st);
 hipError_t launch_dem(const Batch& b, int np_max, int np_rows, int n_sub_max, hipStream_t st);
 }  // namespace lbm
@@ -280,6 +280,7 @@ struct SimHost {
   double Rmax;
   int march = 0;  // marching depth set by hand, 0: the default
   int solo = 0;   // marching depth of launches over this simulation alone
+  long long own_blocks = 0;  // blocks of the particles' mask boxes (radii at creation)
 };
 
 // Per-phase timing with HIP events on the context's stream: per step six
@@ -325,6 +326,7 @@ struct lbm_ctx {
   int2* d_pmap = nullptr;
   unsigned nblk = 0;
   int np_rows = 0, np_max = 0, Bmax = 0, Bcap_max = 0, npts = 0, n_sub_max = 1;
+  long long own_blocks = 0;
   bool cap_needed = false;  // some simulation with particles has a capillary force
   size_t fresh_cap_max = 0;
   unsigned mnblk = 0;  // blocks of the moments pass over the batch
@@ -531,6 +533,7 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
   ctx->cap_needed = false;
   ctx->n_sub_max = 1;
   ctx->fresh_cap_max = 0;
+  ctx->own_blocks = 0;
   for (int si = 0; si < n_sims; ++si) {
     const SimHost& sh = ctx->sims[si];
     tab[si] = sh.d;
@@ -542,6 +545,7 @@ static int upload_tables(lbm_ctx* ctx, size_t off) {
     blk[si + 1] = (uint32_t)nb;
     for (int p = 0; p < sh.d.np; ++p) pmap.push_back(make_int2(si, p));
     ctx->np_max = std::max(ctx->np_max, sh.d.np);
+    ctx->own_blocks += sh.own_blocks;
     if (sh.d.np > 0) ctx->n_sub_max = std::max(ctx->n_sub_max, sh.d.n_sub);
     if (sh.d.np > 0) {
       ctx->Bmax = std::max(ctx->Bmax, sh.L.Bmask);
@@ -572,7 +576,8 @@ static int post_dem_pipeline(lbm_ctx* ctx, int si, bool with_release) {
   Batch b = batch_one(ctx, si);
   b.fc = 2;
   if (s.np > 0)
-    HIPCHK(ctx, launch_mask_update(b, s.np, s.np, sh.L.Bmask, with_release, ctx->stream));
+    HIPCHK(ctx, launch_mask_update(b, s.np, s.np, sh.L.Bmask, sh.own_blocks, with_release,
+                                   ctx->stream));
   HIPCHK(ctx, launch_boundary(b, ctx->storage, sim_blocks(s), s.fresh_cap, s.np, ctx->stream));
   return LBM_OK;
 }
@@ -649,6 +654,7 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     SimHost& sh = ctx->sims[si];
     sh.cfg = c;
     sh.Rmax = max_radius(c, pp);
+    for (int p = 0; p < c.n_particles; ++p) sh.own_blocks += box_blocks(2.0 * pp[p].R + 4.0);
     sh.L = layout(c, sh.Rmax, history_steps, off);
     off = sh.L.total;
     SimDev& d = sh.d;
@@ -770,7 +776,8 @@ int lbm_create(const lbm_config* cfg, int32_t n_sims, const float* const* phi0,
     const Batch b1 = batch_one(ctx, si);
     hipStream_t st = ctx->stream;
     if (launch_init_mask(d, st) != hipSuccess) return fail(LBM_EHIP, "mask init failed");
-    if (d.np > 0 && launch_mask_update(b1, d.np, d.np, sh.L.Bmask, false, st) != hipSuccess)
+    if (d.np > 0 &&
+        launch_mask_update(b1, d.np, d.np, sh.L.Bmask, sh.own_blocks, false, st) != hipSuccess)
       return fail(LBM_EHIP, "mask build failed");
     if (launch_init_pops(d, d.pops[0], st) != hipSuccess)
       return fail(LBM_EHIP, "population init failed");
@@ -807,7 +814,7 @@ static int step_once(lbm_ctx* ctx, int slot) {
   // without surface tension (sigma = 0) the capillary force is zero: the DEM
   // reads the accumulators it cleared itself
   HIPCHK(ctx, launch_fused(b, ctx->storage, ctx->nblk, ctx->cap_needed ? ctx->np_rows : 0,
-                           ctx->Bcap_max, st));
+                           ctx->Bcap_max, ctx->own_blocks, st));
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][2], st));
   HIPCHK(ctx, launch_links(b, ctx->storage, ctx->np_rows, ctx->Bmax,
                            ctx->cap_needed ? ctx->npts : 0, st));
@@ -817,7 +824,8 @@ static int step_once(lbm_ctx* ctx, int slot) {
   const Batch a = batch_all(ctx);
   if (ctx->np_rows > 0) {
     HIPCHK(ctx, launch_dem(a, ctx->np_max, ctx->np_rows, ctx->n_sub_max, st));
-    HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->np_max, ctx->Bmax, true, st));
+    HIPCHK(ctx, launch_mask_update(a, ctx->np_rows, ctx->np_max, ctx->Bmax, ctx->own_blocks, true,
+                                   st));
   }
   if (slot >= 0) HIPCHK(ctx, hipEventRecord(P.ev[slot][4], st));
   HIPCHK(ctx, launch_moments(a, ctx->storage, ctx->mnblk, ctx->fresh_cap_max, ctx->np_max, st));
@@ -963,7 +971,7 @@ int lbm_autotune(lbm_ctx* ctx, int32_t reps, int32_t* chosen) {
         for (int r = 0; r <= reps; ++r) {  // the first pass warms up
           if (r == 1) HIPCHK(ctx, hipEventRecord(e0, st));
           HIPCHK(ctx, launch_interface(b1, mom_blocks(d), st));
-          HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, 0, st));
+          HIPCHK(ctx, launch_fused(b1, ctx->storage, nb, 0, 0, 0, st));
           HIPCHK(ctx, launch_moments(a1, ctx->storage, mom_blocks(d), 0, 0, st));
         }
         HIPCHK(ctx, hipEventRecord(e1, st));

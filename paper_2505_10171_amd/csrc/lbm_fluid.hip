@@ -1065,16 +1065,24 @@ __global__ __launch_bounds__(256)
 }
 
 // per-particle box of (phi, G) at the nodes the Lagrangian points interpolate
-// (G after the wetting rotation, from the step's normal field)
+// (G after the wetting rotation, from the step's normal field): of a box of the
+// simulation's side B the nodes from floor(x - R) to floor(x + R) + 1 per axis, the
+// largest sphere's being the whole (one sphere of radius 20 beside 400 of radius 3, with
+// the fused step: 425 us with whole boxes for all, 391 as a launch of their own, 154 so).
 // block `block` of the `blocks` of particle p
 __device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, int p, int block,
                                               int blocks) {
   DevParticle& P = s.P[p];
   const int B = s.cap_B;
-  int org[3];
+  int org[3], w[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) org[k] = (int)floor(P.x[k] - P.R);
-  if (s.cap_pref == 0.0) return;  // no surface tension: no capillary force
+  for (int k = 0; k < 3; ++k) {
+    org[k] = (int)floor(P.x[k] - P.R);
+    w[k] = min((int)floor(P.x[k] + P.R) + 2 - org[k], B);
+  }
+  const int vol = w[0] * w[1] * w[2];
+  // (no surface tension: no capillary force)
+  if (s.cap_pref == 0.0 || block * 256 >= vol) return;
   float4* box = s.capbox + (long long)p * B * B * B;
   // the record's fields held in registers (the box stores may alias the record)
   const int nx = s.nx, ny = s.ny, nz = s.nz, N = (int)s.N;
@@ -1086,8 +1094,8 @@ __device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, 
   // would fail the |G| > EPS_G test of the force kernel (the 0.99 margin covers
   // rounding); the box's nodes say so here, once, for that kernel
   bool iface = false;
-  for (int k = block * 256 + (int)threadIdx.x; k < B * B * B; k += blocks * 256) {
-    const int ix = k % B, iy = (k / B) % B, iz = k / (B * B);
+  for (int k = block * 256 + (int)threadIdx.x; k < vol; k += blocks * 256) {
+    const int ix = k % w[0], iy = (k / w[0]) % w[1], iz = k / (w[0] * w[1]);
     const int x = wrapi(org[0] + ix, nx), y = wrapi(org[1] + iy, ny), z = wrapi(org[2] + iz, nz);
     const unsigned n = (unsigned)(x + nx * (y + ny * z));
     // every plane read at once and the solid case taken by selects (a load
@@ -1102,7 +1110,7 @@ __device__ __forceinline__ void capillary_box(const Batch& bt, const SimDev& s, 
     const float gm = fmaxf(gw, EPS_G);
     const float4 v = make_float4(fl ? ph : 2.f, mixed ? n0 * gm : 0.f, mixed ? n1 * gm : 0.f,
                                  mixed ? n2 * gm : 0.f);
-    box[k] = v;
+    box[ix + B * (iy + B * iz)] = v;
     iface |= v.x <= 1.5f && v.y * v.y + v.z * v.z + v.w * v.w > (0.99f * EPS_G) * (0.99f * EPS_G);
   }
   if (__syncthreads_or(iface) && threadIdx.x == 0) P.cap_on = 1;
@@ -1459,6 +1467,10 @@ __device__ __forceinline__ void capillary_block(const SimDev& s, int p, int bloc
 // forces the row's blocks from link_blocks on sum those, which need nothing of the
 // others (the dependent chains of both hide each other's: one sphere 11.5 + 8 -> 11 us, 20
 // spheres 14 + 5 -> 15.7, 500 spheres 77 + 25 -> 81).
+// The grid is sized by the largest sphere; a block past its particle's box leaves at once
+// (one sphere of radius 20 beside 400 of radius 3: 230 -> 136 us.  Blocks that take
+// several turns instead need 196 VGPRs for 116: 79 us there, but 1,000 spheres of radius 8
+// 314 -> 473).
 template <int STORE>
 __global__ __launch_bounds__(256) void k_links(Batch bt, int link_blocks) {
   __shared__ union {
@@ -1503,9 +1515,10 @@ __global__ __launch_bounds__(256) void k_links(Batch bt, int link_blocks) {
     }
   }
   const int vol = w[0] * w[1] * w[2];
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if ((int)(blockIdx.x * blockDim.x) >= vol) return;
   double acc[6] = {0, 0, 0, 0, 0, 0};
   bool any = false;
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k < vol) {
     const int gx = wrapi(lo[0] + k % w[0], nx);
     const int gy = wrapi(lo[1] + (k / w[0]) % w[1], ny);
@@ -1613,13 +1626,13 @@ hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
 }
 
 // cap_rows particle rows (0: none) fill their capillary boxes of at most Bcap nodes
-// a side, in a step
+// a side, in a step; own: blocks that the particles' own boxes take
 hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows, int Bcap,
-                        hipStream_t st) {
+                        long long own, hipStream_t st) {
   const dim3 t(256);
   float* const no = nullptr;
   if (storage == 0) {
-    const int cap_blocks = capillary_blocks(nblk, cap_rows, Bcap);
+    const int cap_blocks = particle_blocks_flat(nblk, cap_rows, Bcap, own);
     const dim3 grid(nblk + (unsigned)cap_rows * (unsigned)cap_blocks);
     if (b.open)
       hipLaunchKernelGGL((k_fused<0, MODE_STEP, true>), grid, t, 0, st, b, cap_rows, cap_blocks, no,
@@ -1629,7 +1642,7 @@ hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows
                          no, no, no, no);
   } else {
     if (cap_rows > 0)
-      hipLaunchKernelGGL(k_capbox, dim3((unsigned)capillary_blocks(0, 1, Bcap), (unsigned)cap_rows),
+      hipLaunchKernelGGL(k_capbox, dim3((unsigned)particle_blocks(cap_rows, Bcap, own), (unsigned)cap_rows),
                          t, 0, st, b);
     if (b.open)
       hipLaunchKernelGGL((k_fused<1, MODE_STEP, true>), dim3(nblk), t, 0, st, b, 0, 0, no, no, no,

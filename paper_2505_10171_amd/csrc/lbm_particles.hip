@@ -1137,11 +1137,12 @@ hipError_t launch_push(const SimDev& s, hipStream_t st) {
   return hipGetLastError();
 }
 
-// np_max: the most particles of one simulation of the batch
-hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, bool with_release,
-                              hipStream_t st) {
+// np_max: the most particles of one simulation of the batch; own: blocks that the
+// particles' own boxes take
+hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax, long long own,
+                              bool with_release, hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
-  dim3 grid(particle_blocks(np_rows, Bmax), np_rows);
+  dim3 grid(particle_blocks(np_rows, Bmax, own), np_rows);
   if (!mask_by_search(np_max)) {
     hipLaunchKernelGGL(k_claim, grid, dim3(256), 0, st, b);
     if (with_release) hipLaunchKernelGGL(k_release, grid, dim3(256), 0, st, b);

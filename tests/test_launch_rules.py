@@ -26,17 +26,16 @@ def rule(tmp_path_factory):
     return run
 
 
-@pytest.mark.parametrize("nodes,rows,R", [
-    (32 ** 3, 1, 4), (512 * 256 * 192, 500, 4), (256 ** 3, 4096, 10),
+@pytest.mark.parametrize("nodes,rows,R,r", [
+    (32 ** 3, 1, 4, 4), (512 * 256 * 192, 500, 4, 4), (256 ** 3, 4096, 10, 10),
     # grids beyond one dimension with a node per thread
-    (240 ** 3, 501, 102), (256 ** 3, 1281, 80), (226 * 10 ** 6, 4096, 60)])
-def test_capillary_blocks_fit_the_grid(rule, nodes, rows, R):
-    side, fluid = 2 * R + 3, -(-nodes // 256)
-    per, = rule(f"capillary_blocks({fluid}, {rows}, {side})")
-    full = -(-side ** 3 // 256)
-    assert 1 <= per <= full and fluid + rows * per <= GRID_BLOCKS
-    # a node per thread wherever that fits
-    assert per == full or fluid + rows * (per + 1) > GRID_BLOCKS
+    (240 ** 3, 501, 102, 3), (256 ** 3, 1281, 80, 10), (226 * 10 ** 6, 4096, 60, 60)])
+def test_capillary_blocks_fit_the_grid(rule, nodes, rows, R, r):
+    """Those of all particles, one of radius R and the others r, share a flat grid with
+    the fluid's."""
+    fluid, own = -(-nodes // 256), f"box_blocks({2 * R + 4}) + {rows - 1} * box_blocks({2 * r + 4})"
+    per, = rule(f"particle_blocks_flat({fluid}, {rows}, {2 * R + 3}, {own})")
+    assert 1 <= per <= -(-(2 * R + 3) ** 3 // 256) and fluid + rows * per <= GRID_BLOCKS
 
 
 def test_where_a_kernel_stores_directly(rule):
@@ -48,11 +47,16 @@ def test_where_a_kernel_stores_directly(rule):
     assert got == [1, 1, 0, 0, 0, 0, 0, 0]
 
 
-@pytest.mark.parametrize("rows,R", [(1, 4), (500, 4), (1, 100), (401, 20), (4096, 10), (60000, 3)])
-def test_particle_blocks(rule, rows, R):
-    side = 2 * R + 4
-    per, = rule(f"particle_blocks({rows}, {side})")
-    full = -(-side ** 3 // 256)
-    assert 1 <= per <= full
-    assert per == 1 or rows * per <= 32768
-    assert per == full or rows * (per + 1) > 32768
+@pytest.mark.parametrize("rows,R,r", [
+    (1, 4, 4), (500, 4, 4), (1, 100, 100), (4096, 10, 10), (500, 12, 12), (401, 20, 3),
+    (512, 14, 2), (60000, 30, 1)])
+def test_particle_blocks(rule, rows, R, r):
+    """A node per thread where the boxes are alike, a bounded grid where one is far
+    larger than the others."""
+    full = -(-(2 * R + 4) ** 3 // 256)
+    own = full + (rows - 1) * -(-(2 * r + 4) ** 3 // 256)
+    per, = rule(f"particle_blocks({rows}, {2 * R + 4}, {own})")
+    if R == r or rows * full <= 32768:
+        assert per == full
+    else:
+        assert per == max(1, 32768 // rows)
