@@ -780,9 +780,10 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
   // queued, and all of up to two planes take it at once, a thread each.  Each
   // thread for its own two entries as they came, a block passed the chain twice
   // per plane (sphere of radius 10 in 32x32x52: 19.6 -> 14.7 us, a drop on pillars
-  // in 256x128x64 66 -> 43).  In a tube, where the rotated entries are those along
-  // the wall, a row of them in most waves, each thread's own stay the better (27
-  // us against 29 queued).
+  // in 256x128x64 66 -> 43, a layer along the axis of a 320x83x83 tube 60.6 -> 42.0, a
+  // plug in it 40.9 -> 42.2, a drop 34.2 -> 34.3).  One fluid alone has none to turn, and
+  // the queue's registers cost it a wave per SIMD (28.2 us against 25.8): the tube
+  // without surface tension goes without.
   constexpr bool QUEUE = GEO != GEO_TUBE;
   // up: 1 for the upper of two planes that are formed before rotate_wet
   auto normals = [&](int z, int up, auto SOL) {
@@ -1049,10 +1050,10 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
 
 // W64: as for the moments pass
 template <int GEO, bool W64>
-// six waves per SIMD and blocks per CU; with a textured wall five, as its rotation
-// would spill
+// six waves per SIMD and blocks per CU; with the queue of a tube or a textured wall
+// five, as the rotation would spill (a layer in a tube 47.4 -> 42.0 us, a plug 45.6 -> 42.2)
 __global__ __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(GEO == GEO_BOXES ? 5 : 6, 8))) void k_interface(Batch bt) {
+    __attribute__((amdgpu_waves_per_eu(GEO >= GEO_TUBE_WET ? 5 : 6, 8))) void k_interface(Batch bt) {
   __shared__ IfLds lds;
   const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
   const SimDev& s = bt.tab[sb.x];
@@ -1622,6 +1623,7 @@ static hipError_t launch_interface_geo(const Batch& b, unsigned mnblk, hipStream
 hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
   if (b.geometry == GEO_PLAIN) return launch_interface_geo<GEO_PLAIN>(b, mnblk, st);
   if (b.geometry == GEO_TUBE) return launch_interface_geo<GEO_TUBE>(b, mnblk, st);
+  if (b.geometry == GEO_TUBE_WET) return launch_interface_geo<GEO_TUBE_WET>(b, mnblk, st);
   return launch_interface_geo<GEO_BOXES>(b, mnblk, st);
 }
 
