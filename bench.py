@@ -12,9 +12,12 @@ One JSON line:
 - roofline: the fused-step group (k_interface, k_fused, k_links, k_moments:
   the population and interface traffic of the step) against the method's
   algorithmic bytes per node-step, 314 B in FP32 (every population of f and g
-  read and written once, phi written and read once, the mask read once), from
-  HIP events recorded on the library's stream inside the timed steps, with a
-  sub-entry per kernel against its own bytes;
+  read and written once, phi written and read once, the mask read once), or
+  what the kernels move there where that is less: on tile planes of one pure
+  fluid (counted over the same steps; most of the box in a run's first
+  hundreds of steps, then few), from HIP events recorded on the library's
+  stream inside the timed steps, with a sub-entry per kernel against its own
+  bytes; "window" names the steps;
 - fp16: the same run with FP16 population storage (162 B per node-step), and
   its fields' distance to the FP32 run after the timed steps;
 - c2: the 256x128x96 drop-sweep workload (20 spheres), FP32;
@@ -52,36 +55,120 @@ COUNTERS = {"fp32": os.path.join(ROOT, "profiles",
 GROUP_KERNELS = ("k_interface", "k_fused<", "k_links<", "k_moments<")
 
 
-def kernel_bytes(storage, N, n_fluid):
-    """Algorithmic bytes per launch of each timed phase of the group, each
-    counting what that kernel must read and write once:
+def plane_classes(phi, mask, open_x=False):
+    """Fluid and solid nodes of the interface pass's tile planes by what they hold
+    (tensors (nz, ny, nx)): {"mixed", "pure", "pure_solid": (fluid, solid)}.  A tile
+    plane is pure if phi is exactly +1, or exactly -1, at every fluid node of the tile
+    grown by two nodes and of the two planes below and above; pure_solid: with solid
+    nodes (or an open end) among those."""
+    import torch
+    nz, ny, nx = phi.shape
+    w = next((w for w in (64, 32) if 100 * -(-nx // w) * w <= 120 * nx), 16)
+    h = 256 // w
+    solid = mask != 0
+    what = (~solid & (phi == 1), ~solid & (phi == -1), ~solid & (phi.abs() != 1), solid)
+    out = {"mixed": [0, 0], "pure": [0, 0], "pure_solid": [0, 0]}
+    dev = phi.device
+    for y0 in range(0, ny, h):
+        ys = torch.arange(y0 - 2, y0 + h + 2, device=dev) % ny
+        rows = [b[:, ys].any(1) for b in what]
+        n_solid = solid[:, y0:y0 + h].sum(1)
+        height = min(h, ny - y0)
+        for x0 in range(0, nx, w):
+            xs = torch.arange(x0 - 2, x0 + w + 2, device=dev)
+            end = bool(open_x) and bool(((xs < 0) | (xs >= nx)).any())
+            if open_x:
+                xs = xs[(xs >= 0) & (xs < nx)]
+            a, b, o, s = (r[:, xs % nx].any(1) for r in rows)
+            a, b, o, s = (torch.stack([t.roll(k) for k in range(-2, 3)]).any(0)
+                          for t in (a, b, o, s))
+            mixed = o | (a & b)
+            with_solid = ~mixed & (s | end)
+            ns = n_solid[:, x0:x0 + w].sum(1)
+            n = height * min(w, nx - x0)
+            for key, sel in (("mixed", mixed), ("pure_solid", with_solid),
+                             ("pure", ~mixed & ~with_solid)):
+                k, m = int(sel.sum()), int(ns[sel].sum())
+                out[key][0] += k * n - m
+                out[key][1] += m
+    return {k: tuple(v) for k, v in out.items()}
+
+
+def kernel_bytes(storage, planes):
+    """Bytes per launch of each timed phase of the group, what that kernel must read
+    and write once, by the nodes of `planes` (plane_classes; means over a run's steps):
     interface (k_interface): phi read, the normal (3 components + |G|) and
         the CSF coefficient with the solid-link word written: 4 + 16 + 8 = 28 B
-        per node;
+        per node; with FP32 on pure planes phi alone, with solids the word too;
     fused: per fluid node the 19 stored populations read and written (4 B
         each, 2 B in FP16), the normal (12 B), the curvature word (8 B) and phi
         (4 B); FP16 adds the two reference densities (8 B); per solid node the
-        curvature word (8 B);
+        curvature word (8 B); with FP32 on pure planes the populations, with
+        solids the link word (4 B);
     moments: the 19 populations read, the colliding state's (rho, phi, normal)
-        read (20 B), the mask (2 B), the new (rho, phi) written (8 B).
-    k_links has O(particle links) work and no per-node bytes."""
+        read (20 B), the mask (2 B), the new (rho, phi) written (8 B); on pure planes
+        with FP32 the mask and phi, with FP16 the populations, their reference
+        density (4 B), the mask, rho and phi.
+    k_links has O(particle links) work and no per-node bytes.
+    "group": per node the sum of these, or the method's bytes where they are fewer."""
     p = 2 if storage == "fp16" else 4
     ref = 8 if storage == "fp16" else 0
-    return {"interface": 28 * N,
-            "fused": n_fluid * (38 * p + 24 + ref) + (N - n_fluid) * 8,
-            "moments": N * (19 * p + 20 + 2 + 8),
-            "links": None}
+    mixed = (28, 38 * p + 24 + ref, 19 * p + 30), (28, 8, 19 * p + 30)  # fluid, solid
+    if storage == "fp16":
+        pure = (28, mixed[0][1], 19 * p + 14), (28, 8, 10)
+        pure_solid = pure
+    else:
+        pure = (4, 38 * p, 6), (4, 0, 10)
+        pure_solid = (8, 38 * p + 4, 6), (8, 4, 10)
+    out = {"interface": 0, "fused": 0, "moments": 0, "links": None, "group": 0}
+    for key, cls in (("mixed", mixed), ("pure", pure), ("pure_solid", pure_solid)):
+        for n, b in zip(planes[key], cls):
+            for k, v in zip(("interface", "fused", "moments"), b):
+                out[k] += n * v
+            out["group"] += n * min(sum(b), B_ALG[storage])
+    return out
 
 
-def traffic_from_profile(storage):
+def planes_over(work, warmup, steps, samples=9):
+    """Means of plane_classes over the timed steps of a run, from a run of its own."""
+    import torch
+    from paper_2505_10171_amd.lbm import Simulation
+    sim = Simulation(work["cfg"], work["phi0"], work["particles"])
+    marks = sorted({warmup + round(k * steps / (samples - 1)) for k in range(samples)})
+    at, seen = 0, []
+    for m in marks:
+        sim.step(m - at)
+        at = m
+        phi, mask = sim.phi_mask()
+        seen.append(plane_classes(torch.from_numpy(phi).cuda(),
+                                  torch.from_numpy((mask != 0).view("uint8")).cuda(),
+                                  work["cfg"].get("open_x", 0)))
+    sim.close()
+    del sim
+    torch.cuda.empty_cache()
+    # trapezoidal over the marks
+    if len(marks) == 1:
+        return seen[0]
+    wt = [0.0] * len(marks)
+    for k in range(len(marks) - 1):
+        d = 0.5 * (marks[k + 1] - marks[k]) / (marks[-1] - marks[0])
+        wt[k] += d
+        wt[k + 1] += d
+    return {key: tuple(sum(w * s[key][j] for w, s in zip(wt, seen)) for j in range(2))
+            for key in seen[0]}
+
+
+def traffic_from_profile(storage, steps):
     """Measured HBM bytes per step of the group kernels from the committed
-    rocprofv3 counter summary, or None if absent or taken on other sources."""
-    from paper_2505_10171_amd.prof_summary import kernel_sources_hash, read_counters
+    rocprofv3 counter summary, or None if absent, taken on other sources or over
+    another number of steps than the run's (from its start)."""
+    from paper_2505_10171_amd.prof_summary import (counted_launches, kernel_sources_hash,
+                                                   read_counters)
     path = COUNTERS.get(storage)
     if not path or not os.path.exists(path):
         return None
     per, h = read_counters(path)
-    if h != kernel_sources_hash():
+    if h != kernel_sources_hash() or counted_launches(path, "k_fused<") != steps:
         return None
     tot = 0.0
     for k in GROUP_KERNELS:
@@ -92,8 +179,10 @@ def traffic_from_profile(storage):
     return tot
 
 
-def run_lattice(work, steps, warmup):
-    """Time `steps` steps after `warmup`; phases from HIP events every 10th step."""
+def run_lattice(work, steps, warmup, sample=True):
+    """Time `steps` steps after `warmup`; phases from HIP events every 10th step.
+    sample: the tile planes are counted over the timed steps in a run of its own
+    (else, for profiling, in the last state alone)."""
     import torch
     from paper_2505_10171_amd.lbm import Simulation
     cfg = work["cfg"]
@@ -117,25 +206,32 @@ def run_lattice(work, steps, warmup):
     torch.cuda.empty_cache()
     ph = {k: v[0] / max(v[1], 1) for k, v in prof.items()}  # ms per step
     storage = cfg["storage"]
-    kb = kernel_bytes(storage, N, n_fluid)
+    if sample:
+        planes = planes_over(work, warmup, steps)
+    else:
+        planes = plane_classes(torch.from_numpy(fields[2]), torch.from_numpy(
+            (fields[3] != 0).view("uint8")), cfg.get("open_x", 0))
+    kb = kernel_bytes(storage, planes)
     group_ms = sum(ph[k] for k in GROUP)
-    alg = B_ALG[storage] * N
+    alg = kb["group"]
     kernels = {}
     for k in GROUP:
         e = {"avg_ms": round(ph[k], 5)}
         if kb[k] is not None:
             gbs = kb[k] / (ph[k] * 1e-3) / 1e9
-            e.update(alg_bytes=kb[k], achieved_gbs=round(gbs, 1),
+            e.update(alg_bytes=round(kb[k]), achieved_gbs=round(gbs, 1),
                      frac=round(gbs / HBM_PEAK_GBS, 4))
         kernels[k] = e
     achieved = alg / (group_ms * 1e-3) / 1e9
     mlups = N * steps / (t1 - t0) / 1e6
-    traffic = traffic_from_profile(storage)
+    traffic = traffic_from_profile(storage, warmup + steps)
     roof = {"bound": "hbm",
             "kernel": "fused-step group: k_interface + k_fused + k_links + k_moments",
             "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-            "alg_bytes_per_launch": alg, "alg_bytes_per_node": B_ALG[storage],
+            "alg_bytes_per_launch": round(alg), "alg_bytes_per_node": round(alg / N, 1),
+            "window": f"steps {warmup + 1} to {warmup + steps}",
+            "pure_plane_share": round(1.0 - sum(planes["mixed"]) / N, 4),
             "avg_launch_ms": round(group_ms, 5), "kernels": kernels}
     return dict(N=N, n_fluid=n_fluid, mlups=mlups, ms_per_step=(t1 - t0) * 1e3 / steps,
                 phases=ph, roofline=roof, fields=fields,
@@ -336,15 +432,15 @@ def main():
     if args.only:
         if args.only in ("c3", "c3-fp16"):
             r = run_lattice(W.slab_c3(storage="fp16" if args.only == "c3-fp16" else "fp32"),
-                            args.steps, args.warmup)
+                            args.steps, args.warmup, sample=False)
         elif args.only == "c2":
-            r = run_lattice(W.drop_sweep_c2(), args.steps, args.warmup)
+            r = run_lattice(W.drop_sweep_c2(), args.steps, args.warmup, sample=False)
         elif args.only == "table1":
-            r = run_lattice(W.table1_n1(), args.steps, args.warmup)
+            r = run_lattice(W.table1_n1(), args.steps, args.warmup, sample=False)
         elif args.only == "tube":
-            r = run_lattice(W.tube_segre(), args.steps, args.warmup)
+            r = run_lattice(W.tube_segre(), args.steps, args.warmup, sample=False)
         elif args.only == "textured":
-            r = run_lattice(W.textured_wall(), args.steps, args.warmup)
+            r = run_lattice(W.textured_wall(), args.steps, args.warmup, sample=False)
         else:
             r = ensemble(256, args.c4_steps, 4)
             r.pop("gate_fields")

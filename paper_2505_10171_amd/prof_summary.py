@@ -151,6 +151,15 @@ def read_counters(path):
     return out, (h.group(1) if h else None)
 
 
+def counted_launches(path, kernel):
+    """Launches of the first kernel whose name holds `kernel` in a summary written by
+    `counters` (0: none)."""
+    for m in re.finditer(r"^  (\S.*): (\d+) dispatches", open(path).read(), re.M):
+        if kernel in m.group(1):
+            return int(m.group(2))
+    return 0
+
+
 def main():
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="cmd", required=True)
