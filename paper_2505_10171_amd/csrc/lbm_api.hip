@@ -444,9 +444,9 @@ static void default_marches(std::vector<SimHost>& sims) {
 }
 
 static int geometry_of(const lbm_config& c) {
-  if (c.has_wall == LBM_WALL_BOXES) return GEO_BOXES;
+  if (c.has_wall == LBM_WALL_BOXES) return GEO_ANY;
   if (!c.open_x && c.has_wall != LBM_WALL_TUBE) return GEO_PLAIN;
-  return c.sigma > 0.0 ? GEO_TUBE_WET : GEO_TUBE;
+  return c.sigma > 0.0 ? GEO_ANY : GEO_TUBE;
 }
 static Batch batch_all(const lbm_ctx* c) {
   int geometry = GEO_PLAIN, open = 0;

@@ -319,10 +319,9 @@ __host__ __device__ inline bool near_open_end(const SimDev& s, double x, double 
 }
 
 // What the interface kernel of a batch has to know: nothing but planes and
-// particles; open x ends or a tube wall too, without and with surface tension;
-// textured walls as well.  Without surface tension there is mostly one fluid, and
-// nothing for the wetting rotation to turn.
-enum Geometry { GEO_PLAIN = 0, GEO_TUBE = 1, GEO_TUBE_WET = 2, GEO_BOXES = 3 };
+// particles; open x ends or a tube wall too, without surface tension (mostly one fluid,
+// and nothing for the wetting rotation to turn); all geometries.
+enum Geometry { GEO_PLAIN = 0, GEO_TUBE = 1, GEO_ANY = 2 };
 
 // One launch covers a batch of simulations (an ensemble, or a single one).
 // Per-node kernels run 256-node blocks; blk[s] is the first global block of

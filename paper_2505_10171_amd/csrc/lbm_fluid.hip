@@ -58,7 +58,7 @@ __device__ __forceinline__ void wetting_rotate(const SimDev& s, int gx, int gy, 
     nsz = (gz == 1) ? 1.f : -1.f;
     nc = s.wall_neg_cos;
     ns = s.wall_sin;
-  } else if (GEO == GEO_BOXES && wall_nb && s.has_wall == 3) {
+  } else if (GEO == GEO_ANY && wall_nb && s.has_wall == 3) {
     // textured wall: the normal of the nearest point of the solid surface (the
     // plane's top face z = 1/2, or its underside z = nz - 1/2 through the
     // periodic z direction; the boxes grown by half a node), from it to the
@@ -600,7 +600,8 @@ enum { MODE_STEP = 0, MODE_FIELDS = 1 };
 constexpr int IF_PHI = 68 * 8;          // largest tile plane grown by two: (64 + 4)(4 + 4)
 constexpr int IF_NRM = MOM_HALO;  // grown by one: (64 + 2)(4 + 2)
 // GEO: the geometries of the batch, so that the periodic box on a plane carries
-// none of the others' bookkeeping and a tube nothing of a textured wall's.
+// none of the others' bookkeeping and a tube without surface tension no queue of
+// rotations (below) and nothing of a textured wall's.
 // LX: as for the moments pass
 struct IfLds {
   float fring[4][IF_PHI];
@@ -780,8 +781,8 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
   // queued, and all of up to two planes take it at once, a thread each.  Each
   // thread for its own two entries as they came, a block passed the chain twice
   // per plane (sphere of radius 10 in 32x32x52: 19.6 -> 14.7 us, a drop on pillars
-  // in 256x128x64 66 -> 43, a layer along the axis of a 320x83x83 tube 60.6 -> 42.0, a
-  // plug in it 40.9 -> 42.2, a drop 34.2 -> 34.3).  One fluid alone has none to turn, and
+  // in 256x128x64 66 -> 43, a layer along the axis of a 320x83x83 tube 60.6 -> 42.3, a
+  // plug in it 40.9 -> 42.5, a drop 34.2 -> 34.4).  One fluid alone has none to turn, and
   // the queue's registers cost it a wave per SIMD (28.2 us against 25.8): the tube
   // without surface tension goes without.
   constexpr bool QUEUE = GEO != GEO_TUBE;
@@ -1050,10 +1051,10 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
 
 // W64: as for the moments pass
 template <int GEO, bool W64>
-// six waves per SIMD and blocks per CU; with the queue of a tube or a textured wall
-// five, as the rotation would spill (a layer in a tube 47.4 -> 42.0 us, a plug 45.6 -> 42.2)
+// six waves per SIMD and blocks per CU; with all geometries five, as the rotation would
+// spill (a layer in a tube 47.4 -> 42.3 us, a plug 45.6 -> 42.5)
 __global__ __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(GEO >= GEO_TUBE_WET ? 5 : 6, 8))) void k_interface(Batch bt) {
+    __attribute__((amdgpu_waves_per_eu(GEO == GEO_ANY ? 5 : 6, 8))) void k_interface(Batch bt) {
   __shared__ IfLds lds;
   const int2 sb = batch_block_in(bt, bt.mblk, blockIdx.x);
   const SimDev& s = bt.tab[sb.x];
@@ -1623,8 +1624,7 @@ static hipError_t launch_interface_geo(const Batch& b, unsigned mnblk, hipStream
 hipError_t launch_interface(const Batch& b, unsigned mnblk, hipStream_t st) {
   if (b.geometry == GEO_PLAIN) return launch_interface_geo<GEO_PLAIN>(b, mnblk, st);
   if (b.geometry == GEO_TUBE) return launch_interface_geo<GEO_TUBE>(b, mnblk, st);
-  if (b.geometry == GEO_TUBE_WET) return launch_interface_geo<GEO_TUBE_WET>(b, mnblk, st);
-  return launch_interface_geo<GEO_BOXES>(b, mnblk, st);
+  return launch_interface_geo<GEO_ANY>(b, mnblk, st);
 }
 
 // cap_rows particle rows (0: none) fill their capillary boxes of at most Bcap nodes
