@@ -284,13 +284,12 @@ struct SimHost {
 };
 
 // Per-phase timing with HIP events on the context's stream: per step six
-// events bracket the interface kernels, k_fused, k_links, the other particle
-// kernels and k_moments.  A small ring of
-// event sets is reused; a set is harvested (its elapsed times accumulated)
+// events bracket the interface kernel, k_fused (with the capillary boxes), k_links (with
+// the capillary sums), the DEM and the mask update, and k_moments (with the refill).  A
+// small ring of event sets is reused; a set is harvested (its elapsed times accumulated)
 // before it is recorded again.
 constexpr int PROF_RING = 32;
-// 0 k_fused, 1 particle kernels but k_links, 2 k_moments, 3 k_interface,
-// 4 k_links
+// 0 k_fused, 1 DEM and mask, 2 k_moments, 3 k_interface, 4 k_links
 constexpr int PROF_KINDS = 5;
 constexpr int PROF_EVENTS = PROF_KINDS + 1;
 struct Profiler {

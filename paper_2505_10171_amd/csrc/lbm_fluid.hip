@@ -1644,8 +1644,7 @@ hipError_t launch_fused(const Batch& b, int storage, unsigned nblk, int cap_rows
                          no, no, no, no);
   } else {
     if (cap_rows > 0)
-      hipLaunchKernelGGL(k_capbox, dim3((unsigned)particle_blocks(cap_rows, Bcap, own), (unsigned)cap_rows),
-                         t, 0, st, b);
+      hipLaunchKernelGGL(k_capbox, dim3(particle_blocks(cap_rows, Bcap, own), cap_rows), t, 0, st, b);
     if (b.open)
       hipLaunchKernelGGL((k_fused<1, MODE_STEP, true>), dim3(nblk), t, 0, st, b, 0, 0, no, no, no,
                          no);

@@ -1,5 +1,7 @@
-// lbm_particles.hip -- particle kernels of liblbm for gfx950: solid mask update,
-// capillary force on the Lagrangian surface grid and the DEM (contacts with sliding and rolling friction, velocity Verlet).
+// lbm_particles.hip -- particle kernels of liblbm for gfx950: solid mask update
+// and the DEM (contacts with sliding and rolling friction, velocity Verlet).  The
+// refilling of fresh nodes, the links and the capillary force are in lbm_fluid.hip,
+// whose launches they share.
 #include <algorithm>
 
 #include "launch_rules.h"
@@ -638,7 +640,7 @@ __global__ __launch_bounds__(64) void k_dem_setup(Batch bt, int np_rows, int mas
 
 // The contact force of one active contact whose spring slot sl is known
 // (normal spring-dashpot, sliding and rolling friction after Luding's model as
-// the paper describes it); the same arithmetic as contact().
+// the paper describes it).
 __device__ __forceinline__ void contact_force(const SimDev& s, Contact* sl, double delta,
                                               const double* nh, const double* vi,
                                               const double* wi, const double* vj,

@@ -344,8 +344,9 @@ class Context:
         self._check(load_library().lbm_profile(self.h, int(every) if enable else 0))
 
     def profile_read(self):
-        """{kind: (total_ms, launches)} for the fused, particle (other than
-        the links), moments, interface and link phases."""
+        """{kind: (total_ms, launches)} for the fused (with the capillary boxes),
+        particle (DEM and mask), moments (with the refill), interface and link
+        (with the capillary sums) phases."""
         n = len(PROFILE_KINDS)
         ms = (C.c_double * n)()
         cnt = (C.c_int64 * n)()
