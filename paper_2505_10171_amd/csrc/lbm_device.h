@@ -277,7 +277,12 @@ enum TileKind : uint8_t {
   KIND_PURE_A = 1,  // phi = +1
   KIND_PURE_B = 2,  // phi = -1
   KIND_PURE_A_SOLID = 3,
-  KIND_PURE_B_SOLID = 4
+  KIND_PURE_B_SOLID = 4,
+  // no fluid node in the tile's plane itself, grown by two (a wall): next to mixed
+  // fluids the fused kernel would load the populations of its solid nodes before their
+  // curvature words tell (512 x 512 x 12 on a wall: fused 90.3 us, 86.8 so, as before
+  // there were kinds; moments 73.6 and 67.2)
+  KIND_SOLID = 5
 };
 __device__ __forceinline__ unsigned kind_index(const SimDev& s, int x, int y, int z) {
   return (unsigned)((z * s.mtiles_y + (y >> (8 - s.mtile_lx))) * s.mtiles_x + (x >> s.mtile_lx));

@@ -928,8 +928,9 @@ __device__ __forceinline__ void interface_block(const Batch& bt, const SimDev& s
     const bool pure = pure_class(all & 15u);
     if (t == 0)
       KIND[(z * s_mty + by) * s_mtx + bx] =
-          !pure ? KIND_MIXED
-                : (uint8_t)(((all & 2u) ? KIND_PURE_B : KIND_PURE_A) + ((all & 8u) ? 2 : 0));
+          (hist & 0x700u) == 0u ? KIND_SOLID
+          : !pure ? KIND_MIXED
+                  : (uint8_t)(((all & 2u) ? KIND_PURE_B : KIND_PURE_A) + ((all & 8u) ? 2 : 0));
     if (pure_class(near & 15u))
       zero_normals(z + 1, (near & 8u) != 0u);
     else if (near & 8u)
@@ -1172,7 +1173,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   const int kind =
       STORE ? KIND_MIXED : gp((const uint8_t*)s.kind)[kind_index(s, gx, gy, gz)];
   uint32_t bits = 0u;
-  if (kind >= KIND_PURE_A_SOLID) bits = __float_as_uint(at(cur, 2u * (unsigned)n + 1u));
+  if (kind == KIND_SOLID)
+    bits = 0x80000000u;
+  else if (kind >= KIND_PURE_A_SOLID)
+    bits = __float_as_uint(at(cur, 2u * (unsigned)n + 1u));
   // MODE_FIELDS: the fields that are asked for
   auto put = [&](float r, float ph, float ux, float uy, float uz, float fx, float fy, float fz) {
     if (out_rho) out_rho[n] = r;
