@@ -204,7 +204,8 @@ int lbm_particles_sync(lbm_ctx* ctx, int32_t sim, int32_t dir, lbm_particle* par
 /* Copy fields of simulation sim (bits of lbm_field_bits).  rho, phi: N floats;
  * u: 3N floats; mask: N uint16; pops: 19 ceil(N/64) 64 values of the storage type.  Solid
  * nodes report rho = phi = 0 and u = the solid's surface velocity.  Buffers are
- * host memory unless dst_is_device.  Synchronous. */
+ * host memory unless dst_is_device (device memory of the workspace's GPU is written
+ * by the kernel itself, anything else by a copy).  Synchronous. */
 int lbm_fields(lbm_ctx* ctx, int32_t sim, uint32_t what, float* rho, float* u, float* phi,
                uint16_t* mask, void* pops, int32_t dst_is_device);
 

@@ -112,9 +112,10 @@ def counters(fetch, write, kernels, probe_bytes, out, commands):
 SIMDS, CLOCK_HZ, VALU_CYCLES = 1024, 2.4e9, 4
 
 
-def sq(path, out, commands):
-    """Per-kernel means of every SQ counter in one --pmc run, with per-thread
-    instruction counts and the vector-ALU issue time."""
+def sq(path, out, commands, last=0):
+    """Per-kernel means of every SQ counter in one --pmc run (of the last `last`
+    dispatches, 0: all), with per-thread instruction counts and the vector-ALU
+    issue time."""
     per = {}
     for r in csv.DictReader(open(path)):
         name = short_name(r["Kernel_Name"])
@@ -124,8 +125,10 @@ def sq(path, out, commands):
         lines.append(f"command: {c}")
     lines.append("")
     for name, ctr in per.items():
-        m = {k: statistics.mean(v) for k, v in ctr.items()}
-        lines.append(f"{name}: {len(next(iter(ctr.values())))} dispatches")
+        n = len(next(iter(ctr.values())))
+        m = {k: statistics.mean(v[-last:]) for k, v in ctr.items()}
+        lines.append(f"{name}: " + (f"the last {last} of " if 0 < last < n else "")
+                     + f"{n} dispatches")
         for k in sorted(m):
             lines.append(f"  {k:24s} {m[k]:.4e}")
         waves = m.get("SQ_WAVES", 0.0)
@@ -177,10 +180,11 @@ def main():
     c = sub.add_parser("sq")
     c.add_argument("csv")
     c.add_argument("out")
+    c.add_argument("--last", type=int, default=0)
     c.add_argument("--command", action="append", default=[])
     args = ap.parse_args()
     if args.cmd == "sq":
-        sq(args.csv, args.out, args.command)
+        sq(args.csv, args.out, args.command, args.last)
     elif args.cmd == "stats":
         stats(args.csv, args.out, args.command)
     else:
