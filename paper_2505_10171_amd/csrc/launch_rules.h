@@ -38,8 +38,10 @@ inline int particle_blocks_flat(long long fluid_blocks, long long rows, int side
 // Whether the mask update searches the particles in each block (k_mask, one launch) or
 // claims nodes in memory (three): by the most particles of one simulation, as a search
 // costs about 6 ps per particle and block, the claims 3 to 5 ns per block.  Search against
-// claims: 500 spheres of radius 4 32 and 37 us, 500 of radius 8 97 and 102, 700 of radius
-// 4 45 and 48, 1,000 of radius 8 282 and 192, 4,096 of radius 4 884 and 224.
-inline bool mask_by_search(int np_max) { return np_max <= 512; }
+// claims in a step: 500 spheres of radius 4 32 and 37 us, 500 of radius 8 97 and 102, 700 of
+// radius 4 45 and 48, 1,000 of radius 8 282 and 192, 4,096 of radius 4 884 and 224.
+// After a push, whose many fresh nodes the claims visit in a pass of their own: 1,000 of
+// radius 8 579 and 682, 4,096 of radius 4 886 and 643.
+inline bool mask_by_search(int np_max, bool pushed) { return np_max <= (pushed ? 1024 : 512); }
 
 }  // namespace lbm

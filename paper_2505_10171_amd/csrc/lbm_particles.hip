@@ -1145,7 +1145,7 @@ hipError_t launch_mask_update(const Batch& b, int np_rows, int np_max, int Bmax,
                               bool with_release, hipStream_t st) {
   if (np_rows == 0) return hipSuccess;
   dim3 grid(particle_blocks(np_rows, Bmax, own), np_rows);
-  if (!mask_by_search(np_max)) {
+  if (!mask_by_search(np_max, b.fc == 2)) {
     hipLaunchKernelGGL(k_claim, grid, dim3(256), 0, st, b);
     if (with_release) hipLaunchKernelGGL(k_release, grid, dim3(256), 0, st, b);
     hipLaunchKernelGGL(k_cover, grid, dim3(256), 0, st, b);

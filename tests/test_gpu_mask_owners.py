@@ -81,14 +81,16 @@ def test_more_neighbours_than_the_search_lists(first):
     g.close()
 
 
-@pytest.mark.parametrize("n", [40, 512, 513])
+@pytest.mark.parametrize("n", [40, 512, 513, 1024, 1025])
 def test_many_spheres(n):
     """n spheres of radius 2, 6 nodes apart and jittered, on prescribed paths, then
     pushed so that neighbours overlap; the last two of radius 5 and 14 in a corner of their
     own (14: more nodes than the blocks of a sphere take at once)."""
     r = W.rng(62, n)
-    cfg = W.config(48, 48, 108, has_wall=0, sigma=0.0)
-    sites = [(6 * x + 3, 6 * y + 3, 6 * z + 3) for z in range(9) for y in range(8) for x in range(8)]
+    side = 8 if n <= 513 else 11
+    cfg = W.config(6 * side, 6 * side, 108, has_wall=0, sigma=0.0)
+    sites = [(6 * x + 3, 6 * y + 3, 6 * z + 3)
+             for z in range(9) for y in range(side) for x in range(side)]
     ps = [W.particle(tuple(np.array(sites[k]) + r.uniform(-0.4, 0.4, 3)), 2.0,
                      v=tuple(r.uniform(-0.05, 0.05, 3)), kinematic=1) for k in range(n - 2)]
     ps += [W.particle((40.3, 40.1, 64.2), 5.0, v=(0.06, 0.0, 0.0), kinematic=1),
